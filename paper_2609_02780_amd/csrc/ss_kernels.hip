@@ -3495,134 +3495,93 @@ __global__ __launch_bounds__(256) void k_copy(AppendArgs a) {
 }
 
 // Per (frame, layer, KV head) k-means: farthest-point seeding from the frame
-// mean, then n_iters Lloyd rounds on squared Euclidean distance in fp32.  One
-// block of 16 waves per problem; wave w holds tokens 16w..16w+15 as an MFMA
-// operand tile (bf16 16x16x32, fp32 accumulation).
+// mean, then n_iters Lloyd rounds on squared Euclidean distance in fp32.
 //
 // Exact products, bounded sums: the tokens are exact bf16, and every fp32
 // centre is split exactly into three bf16 parts (c = c1 + c2 + c3), so every
 // product in a dot product is exact and only the fp32 sums round (each addition
 // off by at most 2^-23 relative, whatever the rounding mode of the matrix
-// core).  An expanded distance |x|^2 + |y|^2 - 2 x.y then lies within a bound
-// eps of the exact one (below), and wherever two candidates are closer than
-// 2.5 eps the decision is taken again in the direct form sum_e (x_e - y_e)^2
-// (fmaf in dimension order).  Every decision is therefore the exact one or the
-// direct form's.
+// core).  A distance formed from dot products then lies within a bound eps of
+// the exact one (below), and wherever two candidates are closer than 2.5 eps
+// the decision is taken again in the direct form sum_e (x_e - y_e)^2 (fmaf in
+// dimension order).  Every decision is therefore the exact one or the direct
+// form's.
+//
+// Layout.  What bounds this kernel is the chain of dependent steps (one block
+// barrier per pick, two per round) and, with enough problems on a CU, the
+// matrix cores.  So a problem is a block of only four waves, two blocks share a
+// CU and fill each other's waits, and what never changes stays in registers:
+// wave w holds token tiles w, w + 4, w + 8, w + 12 (16 tokens each) as MFMA
+// operands and, transposed, all tokens of its own 8-dim chunks for the update.
+// Lane (r, c) = (lane >> 4, lane & 15) owns token 16 (w + 4 r) + c.  LDS holds
+// the token rows until the picks are made, then in their place the centres'
+// operands and the one-hot membership.
 //
 // Seeding: pick 0 is the token farthest from the frame mean (direct form).
-// Each later pick is the token whose running minimum of expanded distances to
-// the picks so far is largest (ties to the lower token); eps = 2^-24 max|x|^2
-// (6D + 16).  Candidates near the maximum get their exact minimum over every
-// pick so far.
+// Each later pick is the token whose running minimum of expanded distances
+// |x|^2 + |p|^2 - 2 x.p to the picks so far is largest (ties to the lower
+// token); eps = 2^-24 max|x|^2 (6D + 16).  Candidates near the maximum get
+// their exact minimum over every pick so far.
 //
-// Assignment: per token the two smallest keys (ordered expanded distance, low 6
-// bits = centre) over the centres, reduced over the 16 lanes of an MFMA row by
-// DPP; eps = 2^-24 ((D + 8)(|x|^2 + max|c|^2) + 4 (D + 9) |x| max|c| + d) plus
-// the key truncation.  Near ties are re-decided by one wave, one lane per centre.
+// Assignment: the nearest centre has the largest v = x.c - |c|^2 / 2.  x.c is
+// summed over the first two parts of c only: the third is below 2^-18 |c|, so
+// in d = |x|^2 - 2 v it costs 2^-17 |x||c|, less than the bound on the sums
+// already there, and a third of the matrix work.  The low 6 bits of v carry the
+// centre, so that the best two of 64 values are kept with one max and one
+// median each, and the four row groups of lanes meet by register row swaps.
+// eps = 2^-24 ((D + 16) max|c|^2 + (4 (D + 16) + 128) |x| max|c| + 2 |v|) in d,
+// plus the 6 bits.  Near ties are re-decided by the token's own wave, one lane
+// per centre.
 //
-// Update: the member sums are an MFMA contraction over the tokens (one-hot
-// membership x tokens; exact products, a fixed summation order); a centre moves
-// to sum / count, an empty centre stays.  The new centres are published as
-// fp32 rows, squared norms and split MFMA operands.
-// DPP move of a float / the two smallest of (k1, k2) and the partner's pair
-template <int ctrl>
-__device__ __forceinline__ float km_dpp_f(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xF, 0xF, false));
-}
-template <int ctrl>
-__device__ __forceinline__ void km_pair_min(uint32_t& k1, uint32_t& k2) {
-  const uint32_t o1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k1, ctrl, 0xF, 0xF, false);
-  const uint32_t o2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k2, ctrl, 0xF, 0xF, false);
-  k2 = min(max(k1, o1), min(k2, o2));
-  k1 = min(k1, o1);
-}
-
-constexpr int kKmThreads = 1024;      // 16 waves: one 16-token tile per wave (T <= kMaxTokensCompress = 256)
-constexpr int kKmMeanThreads = 256;   // threads of the frame-mean partial sums
-
+// Update: the member sums are an MFMA contraction over the tokens (tokens x
+// one-hot membership; exact products, a fixed summation order); a centre moves
+// to sum / count, an empty centre stays.  A round in which no token changes its
+// centre leaves every sum as it is, and so does every later one: the rounds end
+// there.
+//
+// Measured (16 problems a frame, d = 128, 196 tokens, 32 centroids, 10 rounds)
+// against a block of 16 waves with the tokens and fp32 centres in LDS (one
+// block per CU, every wave reading every operand): one frame 123 -> 44 us, 600
+// frames 4,507 -> 830 us; 64 frames of equal tokens, where every pick is a near
+// tie, 8,860 -> 610 us.  Clock stamps of one frame: tokens in and transposed
+// 12,400 cycles, 31 picks 47,400 (1,530 each), a round 5,000 + 2,900.
 template <int D>
 struct KmLayout {
   static constexpr int KS = D / 32;        // k-steps of 32 dims
   static constexpr int Q = D / 8;          // 8-dim groups per row
-  static constexpr int XW = D / 2 + 4;     // token row stride in 32-bit words (padded by 16 B)
-  static constexpr int CS = D + 1;         // fp32 centre row stride in floats (conflict-free columns)
+  static constexpr int XW = D / 2 + 4;     // staged token row stride in 32-bit words (padded by 16 B)
   // token rows, padded to whole 32-token MFMA k-steps
   __host__ __device__ static int rows(int T) { return (T + 31) / 32 * 32; }
-  __host__ __device__ static size_t op_bytes(int C) { return (size_t)((C + 15) / 16) * 3 * KS * 64 * 16; }
-  __host__ __device__ static size_t x_bytes(int T) { return (size_t)rows(T) * XW * 4; }
-  // the centre rows also hold the frame mean's partial sums (kKmMeanThreads / Q slices of D)
-  __host__ __device__ static size_t c_bytes(int C) {
-    const size_t n = (size_t)C * CS, m = (size_t)8 * kKmMeanThreads;
-    return (n > m ? n : m) * 4;
+  __host__ __device__ static int tiles(int C) { return (C + 15) / 16; }
+  // the centres' three bf16 parts as MFMA operands
+  __host__ __device__ static size_t op_bytes(int C) { return (size_t)tiles(C) * 3 * KS * 64 * 16; }
+  // one-hot membership operands
+  __host__ __device__ static size_t hot_bytes(int T, int C) { return (size_t)rows(T) / 32 * tiles(C) * 64 * 16; }
+  // the token rows until the picks are made, then operands and membership in their place
+  __host__ __device__ static size_t bytes(int T, int C) {
+    const size_t work = op_bytes(C) + hot_bytes(T, C), stage = (size_t)rows(T) * XW * 4;
+    return work > stage ? work : stage;
   }
-  __host__ __device__ static size_t bytes(int T, int C) { return op_bytes(C) + x_bytes(T) + c_bytes(C); }
 };
 
 __device__ __forceinline__ float bf16f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// Publishes the 8 dims 8q..8q+7 of centre c: the fp32 row (c < C), its exact
-// three-part bf16 split as MFMA A operands, and (lane q == 0) the squared norm
-// summed over the Q lanes of the centre in a fixed butterfly.  Every lane of
-// the wave calls it (inactive items pass zeros and c >= C).
-template <int D>
-__device__ __forceinline__ void km_publish(int c, int q, int C, const float (&v)[8], float* cenf,
-                                           u32x4* opA, float* cn) {
-  using Lay = KmLayout<D>;
-  float ss = 0.f;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) ss = fmaf(v[k], v[k], ss);
-  uint32_t w1[4], w2[4], w3[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    uint16_t p1[2], p2[2], p3[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const float x = v[2 * k + h];
-      p1[h] = bf16_rne(x);
-      const float r1 = x - bf16f(p1[h]);
-      p2[h] = bf16_rne(r1);
-      p3[h] = bf16_rne(r1 - bf16f(p2[h]));
-    }
-    w1[k] = (uint32_t)p1[0] | ((uint32_t)p1[1] << 16);
-    w2[k] = (uint32_t)p2[0] | ((uint32_t)p2[1] << 16);
-    w3[k] = (uint32_t)p3[0] | ((uint32_t)p3[1] << 16);
-  }
-  if (c < (C + 15) / 16 * 16) {
-    const int ct = c >> 4, ln = (c & 15) + 16 * (q & 3), ks = q >> 2;
-    opA[((ct * 3 + 0) * Lay::KS + ks) * 64 + ln] = u32x4{w1[0], w1[1], w1[2], w1[3]};
-    opA[((ct * 3 + 1) * Lay::KS + ks) * 64 + ln] = u32x4{w2[0], w2[1], w2[2], w2[3]};
-    opA[((ct * 3 + 2) * Lay::KS + ks) * 64 + ln] = u32x4{w3[0], w3[1], w3[2], w3[3]};
-  }
-  if (c < C) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) cenf[c * Lay::CS + 8 * q + k] = v[k];
-  }
-  if (Lay::Q == 16) {   // the 16 lanes of the centre are one DPP row; lane q == 0 keeps its sum
-    ss += km_dpp_f<0xB1>(ss);
-    ss += km_dpp_f<0x4E>(ss);
-    ss += km_dpp_f<0x124>(ss);
-    ss += km_dpp_f<0x128>(ss);
-  } else {
-    ss += __shfl_xor(ss, 1);
-    ss += __shfl_xor(ss, 2);
-    ss += __shfl_xor(ss, 4);
-  }
-  if (q == 0 && c < C) cn[c] = ss;
-}
+// LDS pointers (kept in their address space through the out-of-line functions)
+typedef const __attribute__((address_space(3))) uint32_t* lds_u32;
+typedef const __attribute__((address_space(3))) u32x4* lds_u32x4;
 
-// Direct squared distance sum_e (x_e - y_e)^2 (fmaf in dimension order) of a
-// bf16 token row in LDS against another bf16 row, or against fp32 values read
-// by `yv(e)`; 16 dims at a time are loaded ahead of the chain.
+// Direct squared distance sum_e (x_e - y_e)^2 (fmaf in dimension order) of two
+// bf16 rows in LDS; 16 dims at a time are loaded ahead of the chain.
 template <int D>
-__device__ __forceinline__ float km_dist_rows(const uint32_t* xr, const uint32_t* yr) {
+__device__ __forceinline__ float km_dist_rows(lds_u32 xr, lds_u32 yr) {
   float acc = 0.f;
-#pragma unroll
+#pragma unroll 1
   for (int c0 = 0; c0 < D / 8; c0 += 2) {
     u32x4 xa[2], ya[2];
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
-      xa[v] = *reinterpret_cast<const u32x4*>(xr + 4 * (c0 + v));
-      ya[v] = *reinterpret_cast<const u32x4*>(yr + 4 * (c0 + v));
+      xa[v] = *(lds_u32x4)(xr + 4 * (c0 + v));
+      ya[v] = *(lds_u32x4)(yr + 4 * (c0 + v));
     }
 #pragma unroll
     for (int v = 0; v < 2; ++v)
@@ -3636,394 +3595,600 @@ __device__ __forceinline__ float km_dist_rows(const uint32_t* xr, const uint32_t
   }
   return acc;
 }
-template <int D, class YV>
-__device__ __forceinline__ float km_dist_row_f32(const uint32_t* xr, YV yv) {
-  float acc = 0.f;
-#pragma unroll
-  for (int c0 = 0; c0 < D / 8; c0 += 2) {
-    u32x4 xa[2];
-    float y[16];
-#pragma unroll
-    for (int v = 0; v < 2; ++v) xa[v] = *reinterpret_cast<const u32x4*>(xr + 4 * (c0 + v));
-#pragma unroll
-    for (int e = 0; e < 16; ++e) y[e] = yv(8 * c0 + e);
-#pragma unroll
-    for (int v = 0; v < 2; ++v)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float d0 = bf16_lo(xa[v][k]) - y[8 * v + 2 * k];
-        acc = fmaf(d0, d0, acc);
-        const float d1 = bf16_hi(xa[v][k]) - y[8 * v + 2 * k + 1];
-        acc = fmaf(d1, d1, acc);
-      }
-  }
-  return acc;
-}
 
-// Exact (direct-form) minimum squared distance of token `tok` to the picks
-// chosen[0..c-1], one lane per pick (c <= 64), reduced over the wave.  Kept out
-// of line: it runs only near ties and would otherwise hold registers in the
-// seeding loop.
+// Exact (direct-form) minimum squared distance of a token to the first c picks,
+// one lane per pick (c <= 64), reduced over the wave; with c <= 32 for two
+// tokens, t0 and t1 in the two halves of the wave (the result holds for the
+// lane's half).
 template <int D>
-__device__ __noinline__ float km_exact_min(const uint32_t* xs, int xw, const int* chosen, int tok, int c) {
+__device__ __forceinline__ float km_exact_min(lds_u32 xs, lds_u32 chosen, int t0, int t1, int c) {
+  constexpr int XW = KmLayout<D>::XW;
   const int lane = threadIdx.x & 63;
-  float m = lane < c ? km_dist_rows<D>(xs + tok * xw, xs + chosen[lane] * xw) : INFINITY;
+  const bool two = c <= 32;
+  const int p = two ? lane & 31 : lane;
+  float m = p < c ? km_dist_rows<D>(xs + (two && lane >= 32 ? t1 : t0) * XW, xs + chosen[p] * XW) : INFINITY;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) m = fminf(m, __shfl_xor(m, o));
+  for (int o = 1; o < 32; o <<= 1) m = fminf(m, __shfl_xor(m, o));
+  if (!two) m = fminf(m, __shfl_xor(m, 32));
   return m;
 }
 
+// The same for one token per lane against picks p0 .. p1 - 1, from minimum m on:
+// where a wave holds many candidates (frames with many equal tokens), their
+// minima are carried from pick to pick.
 template <int D>
-__global__ __launch_bounds__(kKmThreads) void k_kmeans(AppendArgs a) {
+__device__ __forceinline__ float km_exact_min_own(lds_u32 xs, lds_u32 chosen, int tok, int p0, int p1, float m) {
+  constexpr int XW = KmLayout<D>::XW;
+  for (int p = p0; p < p1; ++p) m = fminf(m, km_dist_rows<D>(xs + tok * XW, xs + chosen[p] * XW));
+  return m;
+}
+constexpr int kKmFew = 6;   // candidates of a wave taken row by row (two at a time while c <= 32)
+
+// The nearest centre of a token row in the direct form, one lane per centre (the
+// centre is the exact sum of its parts), ties to the lower centre.  TWO (C <= 32):
+// two rows, one in each half of the wave; the result holds for the lane's half.
+template <int D, bool TWO>
+__device__ __forceinline__ int km_exact_nearest(lds_u32 rows, lds_u32x4 opA, int C) {
+  constexpr int KS = D / 32;
+  const int lane = threadIdx.x & 63, c = TWO ? lane & 31 : lane;
+  lds_u32 row = rows + (TWO && lane >= 32 ? D / 2 : 0);
+  float acc = INFINITY;
+  if (c < C) {
+    acc = 0.f;
+    lds_u32x4 oc = opA + (c >> 4) * 3 * KS * 64 + (c & 15);
+#pragma unroll 2
+    for (int q = 0; q < D / 8; ++q) {
+      const u32x4 x = *(lds_u32x4)(row + 4 * q);
+      const int at = (q >> 2) * 64 + 16 * (q & 3);
+      const u32x4 c1 = oc[at], c2 = oc[KS * 64 + at], c3 = oc[2 * KS * 64 + at];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float d0 = bf16_lo(x[k]) - (bf16_lo(c1[k]) + (bf16_lo(c2[k]) + bf16_lo(c3[k])));
+        acc = fmaf(d0, d0, acc);
+        const float d1 = bf16_hi(x[k]) - (bf16_hi(c1[k]) + (bf16_hi(c2[k]) + bf16_hi(c3[k])));
+        acc = fmaf(d1, d1, acc);
+      }
+    }
+  }
+  int bi = c < C ? c : INT_MAX;
+#pragma unroll
+  for (int o = 1; o < (TWO ? 32 : 64); o <<= 1) {
+    const float v2 = __shfl_xor(acc, o);
+    const int i2 = __shfl_xor(bi, o);
+    if (v2 < acc || (v2 == acc && i2 < bi)) { acc = v2; bi = i2; }
+  }
+  return min(bi, C - 1);
+}
+
+// Row swaps (gfx950): km_swap16 leaves (a0, b0, a2, b2) in a and (a1, b1, a3,
+// b3) in b, km_swap32 (a0, a1, b0, b1) and (a2, a3, b2, b3), where x0..x3 are
+// the rows of 16 lanes of x.
+__device__ __forceinline__ void km_swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void km_swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+// Sum over the four row groups of s[t], t = 0..3; row r of the result holds s[r]'s.
+__device__ __forceinline__ float km_rows_sum(float s0, float s1, float s2, float s3) {
+  km_swap16(s0, s1);
+  km_swap16(s2, s3);
+  float a = s0 + s1, b = s2 + s3;
+  km_swap32(a, b);
+  return a + b;
+}
+// The best two of two pairs (a1 >= a2, b1 >= b2).
+__device__ __forceinline__ void km_best2(float& a1, float& a2, float b1, float b2) {
+  a2 = fmaxf(fminf(a1, b1), fmaxf(a2, b2));
+  a1 = fmaxf(a1, b1);
+}
+template <int ctrl>
+__device__ __forceinline__ float km_dpp_f(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xF, 0xF, false));
+}
+template <int ctrl>
+__device__ __forceinline__ uint32_t km_mov_dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
+}
+// Largest value over the wave (uniform): row steps, then the rows' broadcasts;
+// every step is one max with a DPP operand.
+__device__ __forceinline__ uint32_t km_wave_max_u32(uint32_t v) {
+  v = max(v, km_mov_dpp<0xB1>(v));    // quad_perm 1,0,3,2
+  v = max(v, km_mov_dpp<0x4E>(v));    // quad_perm 2,3,0,1
+  v = max(v, km_mov_dpp<0x124>(v));   // row_ror 4
+  v = max(v, km_mov_dpp<0x128>(v));   // row_ror 8
+  v = max(v, km_mov_dpp<0x142>(v));   // row_bcast 15 (row 0 reads zeros)
+  v = max(v, km_mov_dpp<0x143>(v));   // row_bcast 31
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// Orders a wave's own LDS writes before its later reads of other lanes' data.
+__device__ __forceinline__ void km_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
+
+constexpr int kKmThreads = 256;   // four waves of four 16-token tiles (T <= kMaxTokensCompress = 256)
+
+// A wave's best token of a pick: its value (as an ordered integer) and the
+// token, with kKmNear added when another token of the wave is within the band.
+struct KmBest {
+  uint32_t u;
+  int tok;
+};
+constexpr int kKmNear = 1 << 16;
+
+// NCT: 16-centre tiles, ceil(C / 16).
+template <int D, int NCT>
+__global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
   using Lay = KmLayout<D>;
-  constexpr int KS = Lay::KS, Q = Lay::Q, XW = Lay::XW, CS = Lay::CS;
-  constexpr int NW = kKmThreads / 64;      // one 16-token tile per wave
-  constexpr int SL = kKmMeanThreads / Q;   // token slices of the frame-mean partial sums
-  constexpr int NDT = D / 16;              // dim tiles of the update
+  constexpr int KS = Lay::KS, Q = Lay::Q, XW = Lay::XW;
+  constexpr int WPK = 4 / KS;                    // waves per 32-dim chunk in the update
+  constexpr int NCW = (NCT + WPK - 1) / WPK;     // centre tiles of one wave in the update
   constexpr int MAXS = kMaxTokensCompress / 32;
+  constexpr float kNone = -3.0e38f;              // below every v
   extern __shared__ __align__(16) unsigned char km_dyn[];
-  __shared__ float xn[kMaxTokensCompress];
-  __shared__ __align__(16) int assign_[kMaxTokensCompress];
-  __shared__ int rlist[kMaxTokensCompress];
-  __shared__ float cn[kMaxCentroids];
-  __shared__ int ccount[kMaxCentroids];
+  __shared__ __align__(16) uint32_t wrow[4][D];            // a wave's own two scratch rows
+  __shared__ __align__(16) KmBest best[2][4], bestfix[4];
   __shared__ int chosen[kMaxCentroids];
-  __shared__ float mu[D];
-  __shared__ uint32_t shk[2][NW], shk2[2][NW];
-  __shared__ int shi[2][NW];
-  __shared__ float cval[kMaxTokensCompress];   // exact minima of near-tie candidates
-  __shared__ float xnmax_sh;
-  __shared__ int rcount, pick_sh;
+  __shared__ float xn[kMaxTokensCompress];
+  __shared__ __align__(16) float mu[D];
+  __shared__ __align__(16) float cnp[KS][kMaxCentroids];   // |c|^2, per 32-dim chunk
+  __shared__ int ccount[2][kMaxCentroids];
+  __shared__ int changed[2];
+  __shared__ float wmax[4];
 
   const int b = blockIdx.x;
   const int g = b % a.Hk, fl = b / a.Hk, l = fl % a.L, f = fl / a.L;
   const int T = a.n_tokens, C = min(a.n_centroids, T);
-  const int nct = (C + 15) / 16, Tp = Lay::rows(T), ntt = (T + 15) / 16, nsteps = Tp / 32;
+  const int ntt = (T + 15) / 16, nsteps = (T + 31) / 32;
   const int64_t nT = (int64_t)a.n_frames * T;
   const uint16_t* src = a.src[l] + ((int64_t)g * nT + (int64_t)f * T) * D;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int t = threadIdx.x, lane = t & 63, c16 = lane & 15, rg = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
 
   u32x4* opA = reinterpret_cast<u32x4*>(km_dyn);
-  uint32_t* xs = reinterpret_cast<uint32_t*>(km_dyn + Lay::op_bytes(C));
-  float* cenf = reinterpret_cast<float*>(km_dyn + Lay::op_bytes(C) + Lay::x_bytes(T));
+  unsigned char* hot = km_dyn + Lay::op_bytes(C);
+  uint32_t* xs = reinterpret_cast<uint32_t*>(km_dyn);
 
-  // tokens -> LDS (bf16 rows, padded stride; rows T..Tp-1 zero); padded rows have no centre
-  for (int i = t; i < Tp * Q; i += kKmThreads) {
-    const int r = i / Q, v = i - r * Q;
-    u32x4 x = {0u, 0u, 0u, 0u};
-    if (r < T) x = *reinterpret_cast<const u32x4*>(src + (int64_t)r * D + 8 * v);
-    *reinterpret_cast<u32x4*>(xs + r * XW + 4 * v) = x;
-  }
-  for (int r = t; r < kMaxTokensCompress; r += kKmThreads) assign_[r] = -1;
-  if (t == 0) rcount = 0;
-  __syncthreads();
-  // frame mean: thread (slice s, group q) sums dims 8q..8q+7 over tokens s, s + SL, ...;
-  // the slices' partial sums (staged in the centre rows, unused until seeding ends) are
-  // then added in slice order.  Squared norms |x|^2 in dimension order (fmaf).
-  if (t < kKmMeanThreads) {
-    const int q = t % Q, s = t / Q;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int r = s; r < T; r += SL) {
-      const u32x4 x = *reinterpret_cast<const u32x4*>(xs + r * XW + 4 * q);
-      const uint32_t ws[4] = {x[0], x[1], x[2], x[3]};
+  // token rows -> LDS (rows T.. of the last 32-token step are zero)
+  {
+    const int n = 32 * nsteps * Q;
+    for (int i0 = 0; i0 < n; i0 += 4 * kKmThreads) {
+      u32x4 x[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { acc[2 * k] += bf16_lo(ws[k]); acc[2 * k + 1] += bf16_hi(ws[k]); }
-    }
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u * kKmThreads + t, r = i / Q, v = i - r * Q;
+        x[u] = u32x4{0u, 0u, 0u, 0u};
+        if (r < T) x[u] = *reinterpret_cast<const u32x4*>(src + (int64_t)r * D + 8 * v);
+      }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) cenf[s * D + 8 * q + k] = acc[k];
-  } else if (t < kKmMeanThreads + kMaxTokensCompress) {
-    const int r = t - kKmMeanThreads;
-    float s2 = 0.f;
-    if (r < T) {
-#pragma unroll
-      for (int v = 0; v < Q; ++v) {
-        const u32x4 x = *reinterpret_cast<const u32x4*>(xs + r * XW + 4 * v);
-        const uint32_t ws[4] = {x[0], x[1], x[2], x[3]};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          s2 = fmaf(bf16_lo(ws[k]), bf16_lo(ws[k]), s2);
-          s2 = fmaf(bf16_hi(ws[k]), bf16_hi(ws[k]), s2);
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + u * kKmThreads + t, r = i / Q, v = i - r * Q;
+        if (i < n) *reinterpret_cast<u32x4*>(xs + r * XW + 4 * v) = x[u];
       }
     }
-    xn[r] = s2;
   }
-  __syncthreads();
-  if (t < D) {
-    float acc = 0.f;
-    for (int s = 0; s < SL; ++s) acc += cenf[s * D + t];
-    mu[t] = acc / (float)T;
-  } else if (t >= 64 * 4 && t < 64 * 5) {   // wave 4: the largest squared norm
-    float m = 0.f;
-    for (int r = lane; r < T; r += 64) m = fmaxf(m, xn[r]);
-    const uint32_t mm = wave_max_u32(__float_as_uint(m));   // non-negative floats order as uint
-    if (lane == 0) xnmax_sh = __uint_as_float(mm);
-  }
+  if (t < 2 * kMaxCentroids) ccount[t / kMaxCentroids][t % kMaxCentroids] = 0;
+  if (t < 2) changed[t] = 0;
   __syncthreads();
 
-  // The wave's token tile (tokens 16w..16w+15) as MFMA A operands, kept for seeding
-  // and assignment.  Output lane l holds tokens 16w + 4(l>>4) + j, j = 0..3; lane l
-  // owns token tok_l = 16w + 4(l>>4) + (l&3) (four lanes per token, identical values).
-  const bool has_tile = w < ntt;
-  u32x4 A[KS];
+  // the wave's token tiles (operand column c16, k = dims 8 rg .. of each chunk)
+  u32x4 X[4][KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
-    A[ks] = has_tile ? *reinterpret_cast<const u32x4*>(xs + (16 * w + (lane & 15)) * XW + 16 * ks + 4 * (lane >> 4))
-                     : u32x4{0u, 0u, 0u, 0u};
-  const int my_tok = 16 * w + 4 * (lane >> 4) + (lane & 3);
-  const bool tok_ok = has_tile && my_tok < T;
-  const float my_xn = tok_ok ? xn[my_tok] : 0.f;
-  const float xnmax = xnmax_sh;
+  for (int r = 0; r < 4; ++r) {
+    const int tile = w + 4 * r;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      X[r][ks] = tile < 2 * nsteps ? *reinterpret_cast<const u32x4*>(xs + (16 * tile + c16) * XW + 16 * ks + 4 * rg)
+                                   : u32x4{0u, 0u, 0u, 0u};
+  }
+  // the tokens of the wave's 32-dim chunk as MFMA A operands (row = dim, k =
+  // token): xT[0] holds the even dims 2 i of the chunk in row i, xT[1] the odd
+  // ones, so that output lane (rg, c16) holds the 8 consecutive dims 8 rg ..
+  const int kw = w % KS, cw = w / KS;
+  u32x4 xT[2][MAXS];
+#pragma unroll
+  for (int st = 0; st < MAXS; ++st) {
+    xT[0][st] = xT[1][st] = u32x4{0u, 0u, 0u, 0u};
+    if (st < nsteps) {   // wave-uniform
+      const uint32_t* p = xs + (32 * st + 8 * rg) * XW + 16 * kw + c16;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t w0 = p[(2 * k) * XW], w1 = p[(2 * k + 1) * XW];
+        xT[0][st][k] = (w0 & 0xFFFFu) | (w1 << 16);
+        xT[1][st][k] = (w0 >> 16) | (w1 & 0xFFFF0000u);
+      }
+    }
+  }
 
-  // ---- farthest-point seeding (pick 0 in the direct form, later picks from
-  // MFMA dot products with the exact re-decision near ties)
-  if (t < T) cval[t] = km_dist_row_f32<D>(xs + t * XW, [&](int e) { return mu[e]; });
-  __syncthreads();
-  float val = tok_ok ? cval[my_tok] : -INFINITY;
+  // frame mean (the tokens' sum against a column of ones)
+  {
+    const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < MAXS; ++st)
+      if (st < nsteps) {
+        s0 = mfma_bf16(xT[0][st], ones, s0);
+        s1 = mfma_bf16(xT[1][st], ones, s1);
+      }
+    if (c16 == 0 && cw == 0) {
+      float* m = mu + 32 * kw + 8 * rg;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        m[2 * j] = s0[j] / (float)T;
+        m[2 * j + 1] = s1[j] / (float)T;
+      }
+    }
+  }
+  // squared norms, and the tokens' distances from the mean after the barrier
+  const int my_tok = 16 * (w + 4 * rg) + c16;
+  const bool tok_ok = my_tok < T;
+  float my_xn;
+  {
+    float s[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float x0 = bf16_lo(X[r][ks][k]), x1 = bf16_hi(X[r][ks][k]);
+          s[r] = fmaf(x0, x0, s[r]);
+          s[r] = fmaf(x1, x1, s[r]);
+        }
+    }
+    my_xn = km_rows_sum(s[0], s[1], s[2], s[3]);
+    xn[my_tok] = my_xn;
+    const uint32_t m = km_wave_max_u32(__float_as_uint(my_xn));   // norms order as integers; padded tokens hold 0
+    if (lane == 0) wmax[w] = __uint_as_float(m);
+  }
+  __syncthreads();   // mu, xn and wmax are in
+  const float xnmax = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+  float val;
+  {
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const float4 ma = *reinterpret_cast<const float4*>(mu + 32 * ks + 8 * rg);
+      const float4 mb = *reinterpret_cast<const float4*>(mu + 32 * ks + 8 * rg + 4);
+      const float m[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float d0 = bf16_lo(X[r][ks][k]) - m[2 * k], d1 = bf16_hi(X[r][ks][k]) - m[2 * k + 1];
+          s[r] = fmaf(d0, d0, s[r]);
+          s[r] = fmaf(d1, d1, s[r]);
+        }
+    }
+    val = km_rows_sum(s[0], s[1], s[2], s[3]);
+  }
+
+  // copies the row of the wave's lane `at` (a token tile's column) to LDS
+  auto put_row = [&](uint32_t* dst, int at) {
+    const int rr = at >> 4;   // wave-uniform
+    const bool mine = c16 == (at & 15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (r == rr && mine) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<u32x4*>(dst + 16 * ks + 4 * rg) = X[r][ks];
+      }
+  };
+
+  // ---- farthest-point seeding
   bool avail = tok_ok;
   float my_min = INFINITY;
+  float ex_min = INFINITY;   // the lane's token's exact minimum over picks 0 .. ex_upto - 1
+  int ex_upto = 0;
   const float band = 2.5f * 5.9604645e-8f * xnmax * (float)(6 * D + 16);
   for (int c = 0; c < C; ++c) {
     const int pb = c & 1;
+    const float v = avail ? val : -INFINITY;
     {
-      // wave: largest value, its lowest token, the largest value of any other token
-      const uint32_t o = avail ? ord_u32(val) : 0u;
-      const uint32_t m1 = wave_max_u32(o);
-      const uint64_t bm = __ballot(avail && o == m1);
-      const int blane = bm ? __builtin_ctzll(bm) : 0;
-      const int btok = 16 * w + 4 * (blane >> 4) + (blane & 3);
-      const uint32_t m2 = wave_max_u32(avail && my_tok != btok ? o : 0u);
-      if (lane == 0) {
-        shk[pb][w] = m1;
-        shk2[pb][w] = m2;
-        shi[pb][w] = bm ? btok : INT_MAX;
-      }
+      const uint32_t u = ord_u32(v), m1 = km_wave_max_u32(u);
+      const uint64_t bm = __ballot(u == m1), nm = __ballot(v >= ord_f32(m1) - band);
+      const int bl = __builtin_ctzll(bm);   // the lowest token of the wave's largest
+      if (lane == bl) best[pb][w] = KmBest{m1, my_tok + ((nm & (nm - 1)) ? kKmNear : 0)};
     }
     __syncthreads();
-    // the waves' winners, lane i holding wave i's: the largest, its lowest token,
-    // the largest of everything else (waves without a candidate hold zeros)
-    uint32_t k1, k2;
-    int pick;
+    int tok;
     {
-      const uint32_t a1 = lane < NW ? shk[pb][lane] : 0u, a2 = lane < NW ? shk2[pb][lane] : 0u;
-      const int i1 = lane < NW ? shi[pb][lane] : INT_MAX;
-      k1 = wave_max_u32(a1);
-      pick = (int)wave_min_u32(a1 == k1 ? (uint32_t)i1 : (uint32_t)INT_MAX);
-      k2 = wave_max_u32(max(i1 != pick ? a1 : 0u, a2));
-    }
-    if (c > 0 && k2 != 0u && ord_f32(k2) >= ord_f32(k1) - band) {
-      // near tie: exact minima of the candidates over picks 0..c-1, one wave each
-      if (t == 0) rcount = 0;
-      __syncthreads();
-      const float v1 = ord_f32(k1);
-      if (avail && (lane >> 2 & 3) == 0 && val >= v1 - band) rlist[atomicAdd(&rcount, 1)] = my_tok;
-      __syncthreads();
-      const int ncand = rcount;
-      for (int i = w; i < ncand; i += NW) {
-        const float m = km_exact_min<D>(xs, XW, chosen, rlist[i], c);
-        if (lane == 0) cval[i] = m;
+      // lane i of a quad holds wave i's best
+      const KmBest e = best[pb][lane & 3];
+      uint32_t m = max(e.u, km_mov_dpp<0xB1>(e.u));
+      m = max(m, km_mov_dpp<0x4E>(m));
+      const float k1 = ord_f32(m);
+      const uint64_t bm = __ballot(e.u == m), nm = __ballot(ord_f32(e.u) >= k1 - band);
+      tok = __builtin_amdgcn_readlane(e.tok, (int)__builtin_ctzll(bm));
+      const bool near = tok >= kKmNear || (nm & 0xE & (nm - 1)) != 0;
+      tok &= kKmNear - 1;
+      if (c == 0) {   // equal distances from the mean: the lowest token over the waves
+        uint32_t x = e.u == m ? (uint32_t)(e.tok & (kKmNear - 1)) : UINT32_MAX;
+        x = min(x, km_mov_dpp<0xB1>(x));
+        x = min(x, km_mov_dpp<0x4E>(x));
+        tok = __builtin_amdgcn_readfirstlane((int)x);
       }
-      __syncthreads();
-      if (t == 0) {
+      if (c > 0 && near) {   // the same in every wave
+        // near tie: each wave takes its own candidates' exact minima over picks 0 .. c - 1
+        uint64_t cand = __ballot(v >= k1 - band && avail);
         float bv = -INFINITY;
         int bt = INT_MAX;
-        for (int i = 0; i < ncand; ++i) {
-          const float m = cval[i];
-          const int tok = rlist[i];
-          if (m > bv || (m == bv && tok < bt)) { bv = m; bt = tok; }
+        auto take = [&](float x, int tk) {
+          if (x > bv || (x == bv && tk < bt)) { bv = x; bt = tk; }
+        };
+        auto tok_of = [&](int at) { return 16 * (w + 4 * (at >> 4)) + (at & 15); };
+        if (__popcll(cand) > kKmFew) {
+          ex_min = km_exact_min_own<D>((lds_u32)xs, (lds_u32)chosen, min(my_tok, T - 1), ex_upto, c, ex_min);
+          ex_upto = c;
+          const uint32_t mine = (cand >> lane & 1) ? ord_u32(ex_min) : 0u, x = km_wave_max_u32(mine);
+          take(ord_f32(x), tok_of(__builtin_ctzll(__ballot(mine == x))));   // tokens rise with the lane
+          cand = 0;
         }
-        pick_sh = bt;
+        while (cand) {
+          const int t0 = tok_of(__builtin_ctzll(cand));
+          cand &= cand - 1;
+          const bool two = c <= 32 && cand != 0;
+          const int t1 = two ? tok_of(__builtin_ctzll(cand)) : t0;
+          if (two) cand &= cand - 1;
+          const float x = km_exact_min<D>((lds_u32)xs, (lds_u32)chosen, t0, t1, c);
+          take(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0)), t0);
+          if (two) take(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 32)), t1);
+        }
+        if (lane == 0) bestfix[w] = KmBest{ord_u32(bv), bt};
+        __syncthreads();
+        KmBest fx = bestfix[0];
+#pragma unroll
+        for (int i = 1; i < 4; ++i) {
+          const KmBest o = bestfix[i];
+          if (o.u > fx.u || (o.u == fx.u && o.tok < fx.tok)) fx = o;
+        }
+        tok = min(__builtin_amdgcn_readfirstlane(fx.tok), T - 1);
       }
-      __syncthreads();
-      pick = pick_sh;
     }
-    if (my_tok == pick) avail = false;
-    if (t == 0) chosen[c] = pick;
+    if (my_tok == tok) avail = false;
+    if (t == 0) chosen[c] = tok;
     if (c == C - 1) break;
-    if (has_tile) {   // wave-uniform: dot products with the pick
-      u32x4 B[KS];
+    u32x4 P[KS];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        B[ks] = *reinterpret_cast<const u32x4*>(xs + pick * XW + 16 * ks + 4 * (lane >> 4));
-      f32x4 h = {0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < KS; ++ks) P[ks] = *reinterpret_cast<const u32x4*>(xs + tok * XW + 16 * ks + 4 * rg);
+    const float xp = xn[tok];
+    f32x4 h[4];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) h = mfma_bf16(A[ks], B[ks], h);
-      const float xp = xn[pick];
-      const int j = lane & 3;
-      const float dot = j == 0 ? h[0] : j == 1 ? h[1] : j == 2 ? h[2] : h[3];
-      my_min = fminf(my_min, fmaf(-2.f, dot, my_xn + xp));
-    }
+    for (int r = 0; r < 4; ++r) h[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h[r] = mfma_bf16(P[ks], X[r][ks], h[r]);
+    const float dot = rg == 0 ? h[0][0] : rg == 1 ? h[1][0] : rg == 2 ? h[2][0] : h[3][0];
+    my_min = fminf(my_min, fmaf(-2.f, dot, my_xn + xp));
     val = my_min;
   }
-  __syncthreads();
-  // initial centres: the chosen tokens
-  for (int i = t; i < nct * 16 * Q; i += kKmThreads) {
-    const int c = i / Q, q = i - c * Q;
-    float v[8];
-    if (c < C) {
-      const u32x4 x = *reinterpret_cast<const u32x4*>(xs + chosen[c] * XW + 4 * q);
-      const uint32_t ws[4] = {x[0], x[1], x[2], x[3]};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) { v[2 * k] = bf16_lo(ws[k]); v[2 * k + 1] = bf16_hi(ws[k]); }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = 0.f;
-    }
-    km_publish<D>(c, q, C, v, cenf, opA, cn);
-  }
-  if (t == 0) rcount = 0;
-  __syncthreads();
+  __syncthreads();   // the last pick is in
 
-  const int dt = w % NDT;
+  // ---- the wave's centres: 8 consecutive dims 32 kw + 8 rg .. of centre 16 ct + c16
+  float cen[NCW][8];
+#pragma unroll
+  for (int i = 0; i < NCW; ++i) {
+    const int ct = cw + i * WPK, c = 16 * ct + c16;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) cen[i][k] = 0.f;
+    if (ct < NCT && c < C) {
+      const u32x4 x = *reinterpret_cast<const u32x4*>(xs + chosen[c] * XW + 16 * kw + 4 * rg);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) { cen[i][2 * k] = bf16_lo(x[k]); cen[i][2 * k + 1] = bf16_hi(x[k]); }
+    }
+  }
+  __syncthreads();   // every wave has left the token rows: operands and membership take their place
+  // publishes the wave's part of the centres: three-part operands and squared norms
+  auto publish = [&]() {
+#pragma unroll
+    for (int i = 0; i < NCW; ++i) {
+      const int ct = cw + i * WPK;
+      if (ct >= NCT) continue;   // wave-uniform
+      float ss = 0.f;
+      u32x4 p1, p2, p3;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        uint16_t q1[2], q2[2], q3[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float x = cen[i][2 * k + e];
+          ss = fmaf(x, x, ss);
+          q1[e] = bf16_rne(x);
+          const float r1 = x - bf16f(q1[e]);
+          q2[e] = bf16_rne(r1);
+          q3[e] = bf16_rne(r1 - bf16f(q2[e]));
+        }
+        p1[k] = (uint32_t)q1[0] | ((uint32_t)q1[1] << 16);
+        p2[k] = (uint32_t)q2[0] | ((uint32_t)q2[1] << 16);
+        p3[k] = (uint32_t)q3[0] | ((uint32_t)q3[1] << 16);
+      }
+      u32x4* o = opA + (ct * 3 * KS + kw) * 64 + lane;
+      o[0] = p1;
+      o[KS * 64] = p2;
+      o[2 * KS * 64] = p3;
+      float x0 = ss, x1 = ss;
+      km_swap16(x0, x1);
+      ss = x0 + x1;
+      x0 = x1 = ss;
+      km_swap32(x0, x1);
+      if (rg == 0) cnp[kw][16 * ct + c16] = x0 + x1;
+    }
+  };
+  publish();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int tile = w + 4 * r;   // the wave clears the operand rows of its own tokens
+    if (tile < 2 * nsteps && rg < 2)
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct)
+        *reinterpret_cast<u32x4*>(hot + (size_t)((((tile >> 1) * NCT + ct) * 64) + 32 * (tile & 1) + 16 * rg + c16) * 16) =
+            u32x4{0u, 0u, 0u, 0u};
+  }
+  __syncthreads();
+  // where the lane's token sits in the one-hot operand of centre c
+  const int my_tile = w + 4 * rg;
+  auto hot_at = [&](int c) {
+    return reinterpret_cast<uint16_t*>(hot + (size_t)((((my_tile >> 1) * NCT + (c >> 4)) * 64) + 32 * (my_tile & 1) +
+                                                      16 * (c16 >> 3) + (c & 15)) * 16 + (c16 & 7) * 2);
+  };
+
+  const int ntw = (ntt - w + 3) / 4;   // tiles of this wave that hold tokens (0 or less: none)
+  int cur = -1, last = 0;              // the lane's token's centre; the count buffer of the last round
   for (int it = 0; it < a.n_iters; ++it) {
-    // ---- assignment: MFMA dot products (A = the wave's 16 tokens, B = 16 centres),
-    // expanded distances as keys (ordered distance, low 6 bits = centre), per token
-    // the two smallest keys over the 16 lanes of an MFMA row (DPP), exact
-    // re-decision near ties
-    if (has_tile) {   // wave-uniform
+    const int ib = it & 1;
+    last = ib;
+    // ---- assignment
+    float b1[4], b2[4], cmax = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        A[ks] = *reinterpret_cast<const u32x4*>(xs + (16 * w + (lane & 15)) * XW + 16 * ks + 4 * (lane >> 4));
-      float cmax = 0.f;
-      for (int ct = 0; ct < nct; ++ct) {
-        const int c = ct * 16 + (lane & 15);
-        if (c < C) cmax = fmaxf(cmax, cn[c]);
-      }
-      cmax = fmaxf(cmax, km_dpp_f<0xB1>(cmax));
-      cmax = fmaxf(cmax, km_dpp_f<0x4E>(cmax));
-      cmax = fmaxf(cmax, km_dpp_f<0x124>(cmax));
-      cmax = fmaxf(cmax, km_dpp_f<0x128>(cmax));
-      float xv[4];
-      uint32_t k1[4], k2[4];
+    for (int r = 0; r < 4; ++r) b1[r] = b2[r] = kNone;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        xv[j] = xn[16 * w + 4 * (lane >> 4) + j];
-        k1[j] = 0xFFFFFFFFu;
-        k2[j] = 0xFFFFFFFFu;
-      }
-      for (int ct = 0; ct < nct; ++ct) {
-        const int c = ct * 16 + (lane & 15);
-        const float cc = c < C ? cn[c] : 0.f;
-        f32x4 h = {0.f, 0.f, 0.f, 0.f}, m = {0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < NCT; ++ct) {
+      float hc[4];   // |c|^2 / 2 of centres 16 ct + 4 rg + j
+      {
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) h = mfma_bf16(A[ks], opA[((ct * 3 + 0) * KS + ks) * 64 + lane], h);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) m = mfma_bf16(A[ks], opA[((ct * 3 + 2) * KS + ks) * 64 + lane], m);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) m = mfma_bf16(A[ks], opA[((ct * 3 + 1) * KS + ks) * 64 + lane], m);
+        for (int ks = 0; ks < KS; ++ks) {
+          const float4 p = *reinterpret_cast<const float4*>(&cnp[ks][16 * ct + 4 * rg]);
+          s[0] += p.x; s[1] += p.y; s[2] += p.z; s[3] += p.w;
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float d = fmaf(-2.f, h[j] + m[j], xv[j] + cc);
-          const uint32_t kn = c < C ? ((ord_u32(d) & ~63u) | (uint32_t)c) : 0xFFFFFFFFu;
-          if (kn < k1[j]) { k2[j] = k1[j]; k1[j] = kn; }
-          else k2[j] = min(k2[j], kn);
+          const bool in = ct < NCT - 1 || 16 * ct + 4 * rg + j < C;
+          if (in) cmax = fmaxf(cmax, s[j]);
+          hc[j] = in ? 0.5f * s[j] : -kNone;
         }
       }
+      u32x4 A1[KS], A2[KS];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        km_pair_min<0xB1>(k1[j], k2[j]);
-        km_pair_min<0x4E>(k1[j], k2[j]);
-        km_pair_min<0x124>(k1[j], k2[j]);
-        km_pair_min<0x128>(k1[j], k2[j]);
+      for (int ks = 0; ks < KS; ++ks) {
+        A1[ks] = opA[(ct * 3 * KS + ks) * 64 + lane];
+        A2[ks] = opA[((ct * 3 + 1) * KS + ks) * 64 + lane];
       }
-      // lane (row r, j < 4) decides token 16w + 4r + j
-      const int j = lane & 15, tok = 16 * w + 4 * (lane >> 4) + j;
-      if (j < 4 && tok < T) {
-        const uint32_t b1 = j == 0 ? k1[0] : j == 1 ? k1[1] : j == 2 ? k1[2] : k1[3];
-        const uint32_t b2 = j == 0 ? k2[0] : j == 1 ? k2[1] : j == 2 ? k2[2] : k2[3];
-        const float xx = j == 0 ? xv[0] : j == 1 ? xv[1] : j == 2 ? xv[2] : xv[3];
-        assign_[tok] = b1 != 0xFFFFFFFFu ? (int)(b1 & 63u) : 0;
-        if (b2 != 0xFFFFFFFFu) {
-          const float d1 = ord_f32(b1 & ~63u), d2 = ord_f32(b2 & ~63u);
-          const float eps = 5.9604645e-8f * ((float)(D + 8) * (xx + cmax) +
-                                             (float)(4 * (D + 9)) * sqrtf(xx * cmax) + fabsf(d1));
-          if (!(d2 - d1 > 2.5f * eps + 3.0517578e-5f * fabsf(d2))) rlist[atomicAdd(&rcount, 1)] = tok;
+#pragma unroll
+      for (int rp = 0; rp < 4; rp += 2) {
+        if (rp >= ntw) continue;   // wave-uniform
+        f32x4 h[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int r = 0; r < 2; ++r) h[r] = mfma_bf16(A2[ks], X[rp + r][ks], h[r]);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int r = 0; r < 2; ++r) h[r] = mfma_bf16(A1[ks], X[rp + r][ks], h[r]);
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t low = (uint32_t)(63 - 16 * ct - j - 4 * rg);
+            const float x = __uint_as_float((__float_as_uint(h[r][j] - hc[j]) & ~63u) | low);
+            b2[rp + r] = __builtin_amdgcn_fmed3f(b1[rp + r], b2[rp + r], x);
+            b1[rp + r] = fmaxf(b1[rp + r], x);
+          }
+      }
+    }
+    // the four row groups meet; row r keeps tile r, so that the lane holds its own token's best two
+    {
+      float x1 = b1[0], y1 = b1[1], x2 = b2[0], y2 = b2[1];
+      km_swap16(x1, y1);
+      km_swap16(x2, y2);
+      km_best2(x1, x2, y1, y2);
+      float u1 = b1[2], v1 = b1[3], u2 = b2[2], v2 = b2[3];
+      km_swap16(u1, v1);
+      km_swap16(u2, v2);
+      km_best2(u1, u2, v1, v2);
+      km_swap32(x1, u1);
+      km_swap32(x2, u2);
+      km_best2(x1, x2, u1, u2);
+      b1[0] = x1;
+      b2[0] = x2;
+      float m0 = cmax, m1 = cmax;
+      km_swap16(m0, m1);
+      m0 = m1 = fmaxf(m0, m1);
+      km_swap32(m0, m1);
+      cmax = fmaxf(m0, m1);
+    }
+    int as = min(63 - (int)(__float_as_uint(b1[0]) & 63u), C - 1);
+    {
+      const float xc = sqrtf(my_xn * cmax), vm = fmaxf(fabsf(b1[0]), fabsf(b2[0]));
+      const float eps = 5.9604645e-8f * ((float)(D + 16) * cmax + (float)(4 * (D + 16) + 128) * xc + 2.f * vm);
+      const bool tie = tok_ok && C > 1 && !(2.f * (b1[0] - b2[0]) > 2.5f * eps + 1.2207031e-4f * vm);
+      uint64_t todo = __ballot(tie);
+      while (todo) {   // direct form, one lane per centre
+        const int at0 = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int at1 = NCT <= 2 && todo ? __builtin_ctzll(todo) : at0;
+        put_row(wrow[w], at0);
+        if (NCT <= 2) {
+          put_row(wrow[w] + D / 2, at1);
+          todo &= todo - 1;   // stays 0 where there was no second one
+        }
+        km_wave_sync();
+        const int n = km_exact_nearest<D, NCT <= 2>((lds_u32)wrow[w], (lds_u32x4)opA, C);
+        km_wave_sync();
+        const int n0 = __builtin_amdgcn_readlane(n, 0), n1 = __builtin_amdgcn_readlane(n, 32);
+        as = lane == at0 ? n0 : NCT <= 2 && lane == at1 ? n1 : as;
+      }
+    }
+    if (tok_ok) {
+      if (as != cur) {
+        if (cur >= 0) *hot_at(cur) = 0;
+        *hot_at(as) = 0x3F80;   // bf16 1.0
+      }
+      atomicAdd(&ccount[ib][as], 1);
+    }
+    if (__ballot(tok_ok && as != cur) && lane == 0) changed[ib] = 1;
+    cur = as;
+    __syncthreads();
+    if (!changed[ib]) break;   // the centres stay, and with them every later round
+    // ---- update
+#pragma unroll
+    for (int i = 0; i < NCW; ++i) {
+      const int ct = cw + i * WPK;
+      if (ct >= NCT) continue;   // wave-uniform
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int st = 0; st < MAXS; ++st)
+        if (st < nsteps) {   // wave-uniform
+          const u32x4 oh = *reinterpret_cast<const u32x4*>(hot + (size_t)((st * NCT + ct) * 64 + lane) * 16);
+          s0 = mfma_bf16(xT[0][st], oh, s0);
+          s1 = mfma_bf16(xT[1][st], oh, s1);
+        }
+      const int n = ccount[ib][16 * ct + c16];
+      if (n > 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          cen[i][2 * j] = s0[j] / (float)n;
+          cen[i][2 * j + 1] = s1[j] / (float)n;
         }
       }
     }
-    if (t < kMaxCentroids) ccount[t] = 0;
-    __syncthreads();
-    const int nref = rcount;
-    for (int i = w; i < nref; i += NW) {   // direct form, lane = centre
-      const int tok = rlist[i];
-      float acc = INFINITY;
-      if (lane < C) acc = km_dist_row_f32<D>(xs + tok * XW, [&](int e) { return cenf[lane * CS + e]; });
-      int bi = lane < C ? lane : INT_MAX;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const float v2 = __shfl_xor(acc, o);
-        const int i2 = __shfl_xor(bi, o);
-        if (v2 < acc || (v2 == acc && i2 < bi)) { acc = v2; bi = i2; }
-      }
-      if (lane == 0) assign_[tok] = bi;
-    }
-    __syncthreads();
-    if (t < T) atomicAdd(&ccount[assign_[t]], 1);
-    if (t == 0) rcount = 0;
-    __syncthreads();
-    // ---- update: member sums as an MFMA contraction over the tokens (A = one-hot
-    // membership of 16 centres, B = the wave's 16 dims of the tokens; exact products,
-    // fixed summation order); mean = sum / count, an empty centre stays
-      // the wave's dim tile of the tokens as MFMA B operands for the update (k = 32
-      // tokens per step, column = dim); the tokens never change
-      u32x4 xT[MAXS];
-    #pragma unroll
-      for (int st = 0; st < MAXS; ++st) {
-        xT[st] = u32x4{0u, 0u, 0u, 0u};
-        if (st >= nsteps) continue;   // wave-uniform
-        const int dcol = dt * 16 + (lane & 15), t0 = 32 * st + 8 * (lane >> 4);
-        uint32_t xb[4];
-    #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t w0 = xs[(t0 + 2 * k) * XW + (dcol >> 1)];
-          const uint32_t w1 = xs[(t0 + 2 * k + 1) * XW + (dcol >> 1)];
-          const uint32_t v0 = (dcol & 1) ? (w0 >> 16) : (w0 & 0xFFFFu);
-          const uint32_t v1 = (dcol & 1) ? (w1 >> 16) : (w1 & 0xFFFFu);
-          xb[k] = v0 | (v1 << 16);
-        }
-        xT[st] = u32x4{xb[0], xb[1], xb[2], xb[3]};
-      }
-    for (int ct = w / NDT; ct < nct; ct += NW / NDT) {   // wave-uniform
-      const int crow = ct * 16 + (lane & 15);
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int st = 0; st < MAXS; ++st) {
-        if (st >= nsteps) continue;   // wave-uniform
-        const int t0 = 32 * st + 8 * (lane >> 4);
-        const int4 a0 = *reinterpret_cast<const int4*>(assign_ + t0);
-        const int4 a1 = *reinterpret_cast<const int4*>(assign_ + t0 + 4);
-        const u32x4 oh = {(a0.x == crow ? 0x3F80u : 0u) | (a0.y == crow ? 0x3F800000u : 0u),
-                          (a0.z == crow ? 0x3F80u : 0u) | (a0.w == crow ? 0x3F800000u : 0u),
-                          (a1.x == crow ? 0x3F80u : 0u) | (a1.y == crow ? 0x3F800000u : 0u),
-                          (a1.z == crow ? 0x3F80u : 0u) | (a1.w == crow ? 0x3F800000u : 0u)};
-        acc = mfma_bf16(oh, xT[st], acc);
-      }
-      const int dcol = dt * 16 + (lane & 15);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = ct * 16 + 4 * (lane >> 4) + j;
-        if (c < C) {
-          const int n = ccount[c];
-          if (n > 0) cenf[c * CS + dcol] = acc[j] / (float)n;
-        }
-      }
-    }
-    __syncthreads();
-    for (int i = t; i < nct * 16 * Q; i += kKmThreads) {
-      const int c = i / Q, q = i - c * Q;
-      float v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = c < C ? cenf[c * CS + 8 * q + k] : 0.f;
-      km_publish<D>(c, q, C, v, cenf, opA, cn);
-    }
+    publish();
+    if (t < kMaxCentroids) ccount[ib ^ 1][t] = 0;
+    if (t == 0) changed[ib ^ 1] = 0;
     __syncthreads();
   }
+
   const int64_t drow0 = ((int64_t)l * a.Hk + g) * a.max_rows + a.row0 + (int64_t)f * C;
-  for (int i = t; i < C * D; i += kKmThreads) {
-    const int c = i / D, e = i - c * D;
-    a.dst.keys[(drow0 + c) * D + e] = bf16_rne(cenf[c * CS + e]);
+#pragma unroll
+  for (int i = 0; i < NCW; ++i) {
+    const int ct = cw + i * WPK, c = 16 * ct + c16;
+    if (ct < NCT && c < C) {
+      u32x4 o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        o[k] = (uint32_t)bf16_rne(cen[i][2 * k]) | ((uint32_t)bf16_rne(cen[i][2 * k + 1]) << 16);
+      *reinterpret_cast<u32x4*>(a.dst.keys + (drow0 + c) * D + 32 * kw + 8 * rg) = o;
+    }
   }
-  for (int c = t; c < C; c += kKmThreads) a.dst.counts[drow0 + c] = a.n_iters > 0 ? ccount[c] : 0;
+  for (int c = t; c < C; c += kKmThreads) a.dst.counts[drow0 + c] = a.n_iters > 0 ? ccount[last][c] : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -4393,18 +4558,28 @@ __global__ __launch_bounds__(256) void k_evidence(EvidenceArgs a) {
 
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
+template <int D, int NCT>
+hipError_t launch_kmeans(const AppendArgs& a, int C, hipStream_t st) {
+  // the largest layout the API admits (n_tokens <= 256, n_centroids <= 64) fits in 160 KB
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_kmeans<D, NCT>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)KmLayout<D>::bytes(kMaxTokensCompress, 16 * NCT));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_kmeans<D, NCT>), dim3(a.n_frames * a.L * a.Hk), dim3(kKmThreads),
+                     KmLayout<D>::bytes(a.n_tokens, C), st, a);
+  return hipSuccess;
+}
+
 template <int D>
 hipError_t append_impl(const AppendArgs& a, bool compress, hipStream_t st) {
   hipLaunchKernelGGL(k_unit_means<D>, dim3(a.n_frames, a.L), dim3(256), 0, st, a);
   if (compress) {
     const int C = std::min(a.n_centroids, a.n_tokens);
-    const size_t lds = KmLayout<D>::bytes(a.n_tokens, C);
-    // the largest layout the API admits (n_tokens <= 256, n_centroids <= 64) fits in 160 KB
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_kmeans<D>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)KmLayout<D>::bytes(kMaxTokensCompress, kMaxCentroids));
+    const hipError_t e = C <= 16   ? launch_kmeans<D, 1>(a, C, st)
+                         : C <= 32 ? launch_kmeans<D, 2>(a, C, st)
+                         : C <= 48 ? launch_kmeans<D, 3>(a, C, st)
+                                   : launch_kmeans<D, 4>(a, C, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_kmeans<D>, dim3(a.n_frames * a.L * a.Hk), dim3(kKmThreads), lds, st, a);
   } else {
     const int64_t total = (int64_t)a.L * a.Hk * a.n_frames * a.n_tokens * (D / 8);
     const int grid = (int)std::min<int64_t>(cdiv(total, 256), 8192);
