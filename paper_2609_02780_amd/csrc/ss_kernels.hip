@@ -36,8 +36,9 @@
 //               when a stream's records fit in LDS.
 //   k_maxmin    greedy max-min diversity over the Gram matrix.
 //
-// Append: k_unit_means (pooled keys and the Eq. memory_key descriptor), k_copy (raw rows) or k_kmeans
-// (per-frame k-means compression).
+// Append: k_append (raw rows, pooled keys and the Eq. memory_key descriptor in
+// one pass), or k_kmeans (per-frame k-means compression and the pooled keys) and
+// k_desc (their descriptors).
 //
 // Ordering conventions: a score s maps to an order-preserving uint32 u(s); the
 // composite key (u(s) << 32) | (0xFFFFFFFF - row) sorts descending exactly as
@@ -3387,111 +3388,118 @@ const GramLaunch* gram_launchers() { return gram_table(std::make_integer_sequenc
 // ---------------------------------------------------------------------------
 // Append kernels
 // ---------------------------------------------------------------------------
-// Descriptor (Eq. memory_key): fp32 mean over the frame's raw last-layer tokens,
-// heads flattened head-major, L2-normalised.  Also writes the frame offsets.
-// Per (frame, layer): the mean raw key of every KV head becomes the frame's
-// pooled key of that layer; the last shallow layer's means, flattened
-// head-major and L2-normalised, are the unit descriptor (Eq. memory_key).
-// Grid: (frames, layers).  Thread (slice s, 8-dim group v) sums tokens s, s + S,
-// ... of its group with 16-byte loads (fp32, token order within the slice); the
-// S slices are then added in slice order, so the sums are deterministic.
+constexpr int kAppendThreads = 1024;
+
+// Frame f's descriptor and row offsets; thread t < dim holds element t of the
+// last layer's means, the block's other threads 0.
+__device__ __forceinline__ void unit_desc(const AppendArgs& a, int f, float val, double* red) {
+  const int t = threadIdx.x, dim = a.Hk * a.D;
+  // deterministic block sum of squares (in 64 bits: one rounding of the norm)
+  const double sq = wave_sum_f64((double)val * (double)val);
+  if ((t & 63) == 0) red[t >> 6] = sq;
+  __syncthreads();
+  double tot = 0.0;
+  for (int i = 0; i < (int)blockDim.x / kWave; ++i) tot += red[i];
+  const double inv = tot > 0.0 ? 1.0 / sqrt(tot) : 0.0;
+  if (t < dim) a.dst.desc[(a.frame0 + f) * (int64_t)dim + t] = (float)((double)val * inv);
+  if (t == 0) {
+    a.dst.frame_off[a.frame0 + f + 1] = (int32_t)(a.row0 + (int64_t)(f + 1) * a.rows_per_frame);
+    if (f == 0) a.dst.frame_off[a.frame0] = (int32_t)a.row0;
+  }
+}
+
+// Raw append.  Grid (frames, layers), one pass over the frame's raw keys of the
+// layer: they are stored as index rows (member counts 1), and the mean raw key
+// of every KV head becomes the frame's pooled key of that layer; the last
+// shallow layer's means, flattened head-major and L2-normalised, are the unit
+// descriptor (Eq. memory_key).
+//
+// Bound by memory for a clip and by the chain of load round trips for one
+// frame, so a block takes a whole (frame, layer) with 16 waves and every thread
+// keeps kAppendIt 16-byte loads in flight: thread (head g, slice s, 8-dim group
+// v) sums tokens s, s + S, ... (fp32, token order), and the S slices are then
+// added in slice order, so the sums are deterministic.  16 lanes read a row and
+// a wave consecutive rows.  The rows go out from the registers that the means
+// are summed from.
+// Nontemporal both ways: a clip is larger than the caches and a frame is not
+// read again soon.  Measured (4 layers, 4 KV heads, d = 128, 196 tokens) against
+// a pass for the means and one for the copy: 600 frames 328 -> 174 us (5.6 TB/s
+// read and written; 188 us with temporal accesses), one frame 13.9 -> 8.1 us.
+constexpr int kAppendIt = 7;
 template <int D>
-__global__ __launch_bounds__(256) void k_unit_means(AppendArgs a) {
-  __shared__ float part[256 * 8];   // [slice][dim] partial sums (S * dim = 2048 floats)
-  __shared__ float red[8];
-  const int f = blockIdx.x, l = blockIdx.y;
-  const int T = a.n_tokens, dim = a.Hk * D, G8 = dim / 8;
-  const int S = 256 / G8;           // dim <= kMaxDescDim: G8 <= 128, S >= 2
+__global__ __launch_bounds__(kAppendThreads, 8) void k_append(AppendArgs a, int f_first) {
+  constexpr int Q = D / 8;          // 16-byte chunks per row
+  __shared__ __align__(16) float part[kAppendThreads * 8];   // [head][slice][dim] partial sums
+  __shared__ double red[kAppendThreads / kWave];
+  __shared__ uint32_t redm[kAppendThreads / kWave];
+  const int f = f_first + blockIdx.x, l = blockIdx.y;
+  const int T = a.n_tokens, dim = a.Hk * D;
+  const int S = kAppendThreads / (a.Hk * Q);   // H_kv * D <= 1024: S >= 8
+  const int t = threadIdx.x;
   const int64_t nT = (int64_t)a.n_frames * T;
-  const uint16_t* src = a.src[l];
+  const uint32_t seen = *a.dst.stats;   // the statistic so far (a value that only grows)
   uint32_t amax = 0;   // largest |key element| (the bits of a non-negative float order as integers)
-  if (threadIdx.x < S * G8) {
-    const int v = threadIdx.x % G8, sl = threadIdx.x / G8;
-    const int g = (8 * v) / D, e0 = (8 * v) % D;
-    const uint16_t* p = src + ((int64_t)g * nT + (int64_t)f * T) * D + e0;
+  if (t < S * a.Hk * Q) {
+    const int g = t / (S * Q), r = t - g * S * Q, sl = r / Q, v = r - sl * Q;
+    // byte offsets within a (layer, KV head) of keys stay below 2^31
+    const char* p = reinterpret_cast<const char*>(a.src[l] + ((int64_t)g * nT + (int64_t)f * T) * D + 8 * v);
+    char* o = reinterpret_cast<char*>(
+        a.dst.keys + (((int64_t)l * a.Hk + g) * a.max_rows + a.row0 + (int64_t)f * T) * D + 8 * v);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int t = sl;
-    for (; t + 3 * S < T; t += 4 * S) {
-      u32x4 x[4];
+    for (int t0 = sl; t0 < T; t0 += kAppendIt * S) {
+      u32x4 x[kAppendIt];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const u32x4*>(p + (int64_t)(t + u * S) * D);
+      for (int u = 0; u < kAppendIt; ++u) {
+        x[u] = u32x4{0u, 0u, 0u, 0u};   // rows past the frame add nothing
+        if (t0 + u * S < T) x[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p + (uint32_t)(t0 + u * S) * (2u * D)));
+      }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < kAppendIt; ++u) {
+        if (t0 + u * S < T)
+          __builtin_nontemporal_store(x[u], reinterpret_cast<u32x4*>(o + (uint32_t)(t0 + u * S) * (2u * D)));
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           acc[2 * k] += bf16_lo(x[u][k]);
           acc[2 * k + 1] += bf16_hi(x[u][k]);
           amax = max(amax, max((x[u][k] << 16) & 0x7FFFFFFFu, x[u][k] & 0x7FFF0000u));
         }
-    }
-    for (; t < T; t += S) {
-      const u32x4 x = *reinterpret_cast<const u32x4*>(p + (int64_t)t * D);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        acc[2 * k] += bf16_lo(x[k]);
-        acc[2 * k + 1] += bf16_hi(x[k]);
-        amax = max(amax, max((x[k] << 16) & 0x7FFFFFFFu, x[k] & 0x7FFF0000u));
       }
     }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) part[sl * dim + 8 * v + k] = acc[k];
+    float4* pp = reinterpret_cast<float4*>(part + ((size_t)(g * S + sl) * D + 8 * v));
+    pp[0] = float4{acc[0], acc[1], acc[2], acc[3]};
+    pp[1] = float4{acc[4], acc[5], acc[6], acc[7]};
   }
   amax = wave_max_u32(amax);
-  if ((threadIdx.x & 63) == 0) atomicMax(a.dst.stats, amax);
+  if ((t & 63) == 0) redm[t >> 6] = amax;
+  for (int i = t; i < a.Hk * T; i += kAppendThreads) {
+    const int g = i / T;
+    a.dst.counts[((int64_t)l * a.Hk + g) * a.max_rows + a.row0 + (int64_t)f * T + (i - g * T)] = 1;
+  }
   __syncthreads();
-  float vals[4];
-  float ss = 0.f;
-  for (int k = 0; k < 4; ++k) {
-    const int e = threadIdx.x + k * 256;
-    vals[k] = 0.f;
-    if (e < dim) {
-      float acc = 0.f;
-      for (int sl = 0; sl < S; ++sl) acc += part[sl * dim + e];
-      vals[k] = acc / (float)T;
-      ss = fmaf(vals[k], vals[k], ss);
-    }
+  if (t < kAppendThreads / kWave) {   // lanes of wave 0
+    uint32_t m = redm[t];
+#pragma unroll
+    for (int o = 1; o < kAppendThreads / kWave; o <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    if (t == 0 && m > seen) atomicMax(a.dst.stats, m);
   }
-  float* pooled = a.dst.pooled + ((a.frame0 + f) * a.L + l) * (int64_t)dim;
-  for (int k = 0; k < 4; ++k) {
-    const int e = threadIdx.x + k * 256;
-    if (e < dim) pooled[e] = vals[k];
+  float val = 0.f;
+  if (t < dim) {   // one element a thread (dim <= 1024)
+    const int g = t / D, e = t - g * D;
+    float acc = 0.f;
+    for (int sl = 0; sl < S; ++sl) acc += part[(size_t)(g * S + sl) * D + e];
+    val = acc / (float)T;
+    a.dst.pooled[((a.frame0 + f) * a.L + l) * (int64_t)dim + t] = val;
   }
-  if (l != a.L - 1) return;  // the same for the whole block
-  // deterministic block sum of squares
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  const float tot = red[0] + red[1] + red[2] + red[3];
-  const float inv = tot > 0.f ? 1.0f / sqrtf(tot) : 0.f;
-  float* out = a.dst.desc + (a.frame0 + f) * (int64_t)dim;
-  for (int k = 0; k < 4; ++k) {
-    const int e = threadIdx.x + k * 256;
-    if (e < dim) out[e] = tot > 0.f ? vals[k] * inv : 0.f;
-  }
-  if (threadIdx.x == 0) {
-    a.dst.frame_off[a.frame0 + f + 1] = (int32_t)(a.row0 + (int64_t)(f + 1) * a.rows_per_frame);
-    if (f == 0) a.dst.frame_off[a.frame0] = (int32_t)a.row0;
-  }
+  if (l == a.L - 1) unit_desc(a, f, val, red);   // the same for the whole block
 }
 
-// Raw rows: 16-byte copies into the arena, member counts = 1.
+// The descriptors of compressed frames, from the pooled keys k_kmeans wrote: a
+// block a frame, one element a thread.
 template <int D>
-__global__ __launch_bounds__(256) void k_copy(AppendArgs a) {
-  const int64_t nT = (int64_t)a.n_frames * a.n_tokens;
-  const int64_t per_row = D / 8;
-  const int64_t total = (int64_t)a.L * a.Hk * nT * per_row;
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < total;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t e8 = c % per_row;
-    const int64_t rr = c / per_row;
-    const int64_t r = rr % nT;
-    const int64_t lg = rr / nT;
-    const int g = (int)(lg % a.Hk), l = (int)(lg / a.Hk);
-    const u32x4 v = *reinterpret_cast<const u32x4*>(a.src[l] + ((int64_t)g * nT + r) * D + 8 * e8);
-    const int64_t drow = ((int64_t)l * a.Hk + g) * a.max_rows + a.row0 + r;
-    *reinterpret_cast<u32x4*>(a.dst.keys + drow * D + 8 * e8) = v;
-    if (e8 == 0) a.dst.counts[drow] = 1;
-  }
+__global__ __launch_bounds__(kAppendThreads) void k_desc(AppendArgs a, int f_first) {
+  __shared__ double red[kAppendThreads / kWave];
+  const int f = f_first + blockIdx.x, dim = a.Hk * D, t = threadIdx.x;
+  unit_desc(a, f, t < dim ? a.dst.pooled[((a.frame0 + f) * a.L + a.L - 1) * (int64_t)dim + t] : 0.f, red);
 }
 
 // Per (frame, layer, KV head) k-means: farthest-point seeding from the frame
@@ -3541,8 +3549,9 @@ __global__ __launch_bounds__(256) void k_copy(AppendArgs a) {
 //
 // Measured (16 problems a frame, d = 128, 196 tokens, 32 centroids, 10 rounds)
 // against a block of 16 waves with the tokens and fp32 centres in LDS (one
-// block per CU, every wave reading every operand): one frame 123 -> 44 us, 600
-// frames 4,507 -> 830 us; 64 frames of equal tokens, where every pick is a near
+// block per CU, every wave reading every operand): one frame 123 -> 45 us, 600
+// frames 4,507 -> 880 us (the pooled keys included, once a pass of 146 us of
+// their own); 64 frames of equal tokens, where every pick is a near
 // tie, 8,860 -> 610 us.  Clock stamps of one frame: tokens in and transposed
 // 12,400 cycles, 31 picks 47,400 (1,530 each), a round 5,000 + 2,900.
 template <int D>
@@ -3772,6 +3781,7 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
       }
     }
   }
+  const uint32_t seen = *a.dst.stats;   // the largest |key element| so far (a value that only grows)
   if (t < 2 * kMaxCentroids) ccount[t / kMaxCentroids][t % kMaxCentroids] = 0;
   if (t < 2) changed[t] = 0;
   __syncthreads();
@@ -3817,12 +3827,35 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
       }
     if (c16 == 0 && cw == 0) {
       float* m = mu + 32 * kw + 8 * rg;
+      float m8[8];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        m[2 * j] = s0[j] / (float)T;
-        m[2 * j + 1] = s1[j] / (float)T;
+        m8[2 * j] = s0[j] / (float)T;
+        m8[2 * j + 1] = s1[j] / (float)T;
+      }
+      // the frame's pooled key too
+      float* pm = a.dst.pooled + (((a.frame0 + f) * a.L + l) * (int64_t)a.Hk + g) * D + 32 * kw + 8 * rg;
+#pragma unroll
+      for (int j = 0; j < 8; j += 4) {
+        const float4 q = {m8[j], m8[j + 1], m8[j + 2], m8[j + 3]};
+        *reinterpret_cast<float4*>(m + j) = q;
+        *reinterpret_cast<float4*>(pm + j) = q;
       }
     }
+  }
+  // largest |key element| (as bf16 magnitudes, which order as integers)
+  {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    u16x2 am = {0, 0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          am = __builtin_elementwise_max(am, __builtin_bit_cast(u16x2, X[r][ks][k] & 0x7FFF7FFFu));
+    const uint32_t m = km_wave_max_u32((uint32_t)(am[0] > am[1] ? am[0] : am[1]) << 16);
+    if (lane == 0 && m > seen) atomicMax(a.dst.stats, m);
   }
   // squared norms, and the tokens' distances from the mean after the barrier
   const int my_tok = 16 * (w + 4 * rg) + c16;
@@ -4192,7 +4225,7 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Pooled shallow Q-K ranking: keys pooled per unit at append (k_unit_means),
+// Pooled shallow Q-K ranking: keys pooled per unit at append (k_append),
 // scored against the question's pooled query weights, top-K units.
 // ---------------------------------------------------------------------------
 struct PoolQArgs {
@@ -4572,7 +4605,6 @@ hipError_t launch_kmeans(const AppendArgs& a, int C, hipStream_t st) {
 
 template <int D>
 hipError_t append_impl(const AppendArgs& a, bool compress, hipStream_t st) {
-  hipLaunchKernelGGL(k_unit_means<D>, dim3(a.n_frames, a.L), dim3(256), 0, st, a);
   if (compress) {
     const int C = std::min(a.n_centroids, a.n_tokens);
     const hipError_t e = C <= 16   ? launch_kmeans<D, 1>(a, C, st)
@@ -4580,10 +4612,12 @@ hipError_t append_impl(const AppendArgs& a, bool compress, hipStream_t st) {
                          : C <= 48 ? launch_kmeans<D, 3>(a, C, st)
                                    : launch_kmeans<D, 4>(a, C, st);
     if (e != hipSuccess) return e;
-  } else {
-    const int64_t total = (int64_t)a.L * a.Hk * a.n_frames * a.n_tokens * (D / 8);
-    const int grid = (int)std::min<int64_t>(cdiv(total, 256), 8192);
-    hipLaunchKernelGGL(k_copy<D>, dim3(grid), dim3(256), 0, st, a);
+  }
+  constexpr int kFrames = 1 << 21;   // a launch holds fewer than 2^32 threads
+  for (int64_t f = 0; f < a.n_frames; f += kFrames) {
+    const int n = (int)std::min<int64_t>(kFrames, a.n_frames - f);
+    if (compress) hipLaunchKernelGGL(k_desc<D>, dim3(n), dim3((a.Hk * D + 63) / 64 * 64), 0, st, a, (int)f);
+    else hipLaunchKernelGGL(k_append<D>, dim3(n, a.L), dim3(kAppendThreads), 0, st, a, (int)f);
   }
   return hipGetLastError();
 }
