@@ -4383,144 +4383,221 @@ __global__ void k_zero32(int32_t* p, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-// Sum over a 256-thread block, the same order every time.
-__device__ float block_sum256(float v, float* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
+// Sum over the wave in a fixed order (uniform).
+__device__ __forceinline__ float wave_sum_fixed(float v) {
+  auto mv = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  v += mv(v, std::integral_constant<int, 0xB1>{});    // quad_perm 1,0,3,2
+  v += mv(v, std::integral_constant<int, 0x4E>{});    // quad_perm 2,3,0,1
+  v += mv(v, std::integral_constant<int, 0x124>{});   // row_ror 4
+  v += mv(v, std::integral_constant<int, 0x128>{});   // row_ror 8
+  const int b = __float_as_int(v);
+  const float r0 = __int_as_float(__builtin_amdgcn_readlane(b, 0)), r1 = __int_as_float(__builtin_amdgcn_readlane(b, 16));
+  const float r2 = __int_as_float(__builtin_amdgcn_readlane(b, 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(b, 48));
+  return (r0 + r1) + (r2 + r3);
 }
 
-__global__ __launch_bounds__(256) void k_cluster_assign(AbsorbArgs a) {
-  __shared__ float red[4];
-  const int dim = a.Hk * a.D;   // at most 1024: four elements per thread
-  int nc = a.cl.state[0], ovf = a.cl.state[1];
-  int n = nc > 0 ? a.cl.sizes[nc - 1] : 0;
-  float c[4] = {0.f, 0.f, 0.f, 0.f};
-  if (nc > 0)
-    for (int k = 0; k < 4; ++k) {
-      const int e = threadIdx.x + 256 * k;
-      if (e < dim) c[k] = a.cl.centroids[(size_t)(nc - 1) * dim + e];
-    }
-  for (int u = 0; u < a.n_units; ++u) {
-    const int64_t t = a.f_lo + u;
-    float kv[4] = {0.f, 0.f, 0.f, 0.f};
-    float part = 0.f;
-    for (int k = 0; k < 4; ++k) {
-      const int e = threadIdx.x + 256 * k;
-      if (e < dim) kv[k] = a.desc[(int64_t)u * dim + e];
-      part = fmaf(kv[k], c[k], part);
-    }
-    bool join = false;
-    if (nc > 0) {
-      const float dot = block_sum256(part, red);
-      join = dot >= a.tau;
-      if (!join && nc == a.max_clusters) {
+// One wave: each unit's decision waits for the centroid that the previous one
+// left, so what counts is the length of that chain.  A wave holds the centroid
+// (EPL elements a lane, at lane + 64 k) and sums without barriers, the next kPf
+// units' descriptors are already in registers, and the joined centroid's norm is
+// summed beside the joining dot product.  c <- Norm((n c + k) / (n + 1)) is
+// formed as Norm(n c + k), which is the same.  Measured (50 units of 512
+// elements): 60.6 us with four waves, two barriers a sum and nothing ahead, 17.9
+// us now (0.35 us a unit).
+template <int EPL>
+__global__ __launch_bounds__(kWave) void k_cluster_assign(AbsorbArgs a) {
+  constexpr int kPf = EPL <= 8 ? 8 : 4;
+  constexpr int dim = kWave * EPL;   // H_kv d, a multiple of 64
+  const int lane = threadIdx.x;
+  int nc = __builtin_amdgcn_readfirstlane(a.cl.state[0]), ovf = __builtin_amdgcn_readfirstlane(a.cl.state[1]);
+  int n = nc > 0 ? __builtin_amdgcn_readfirstlane(a.cl.sizes[nc - 1]) : 0;
+  float c[EPL];
+  auto load = [&](float (&v)[EPL], const float* p) {
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) v[k] = p[lane + kWave * k];
+  };
+  auto store_centroid = [&]() {
+#pragma unroll
+    for (int k = 0; k < EPL; ++k) a.cl.centroids[(size_t)(nc - 1) * dim + lane + kWave * k] = c[k];
+    if (lane == 0) a.cl.sizes[nc - 1] = n;
+  };
+#pragma unroll
+  for (int k = 0; k < EPL; ++k) c[k] = 0.f;
+  if (nc > 0) load(c, a.cl.centroids + (size_t)(nc - 1) * dim);
+  float next[kPf][EPL];
+#pragma unroll
+  for (int p = 0; p < kPf; ++p) load(next[p], a.desc + (int64_t)min(p, a.n_units - 1) * dim);
+  const float* ahead = a.desc + (int64_t)min(kPf, a.n_units - 1) * dim;
+  for (int u0 = 0; u0 < a.n_units; u0 += kPf) {
+#pragma unroll
+    for (int p = 0; p < kPf; ++p) {
+      const int u = u0 + p;
+      if (u >= a.n_units) continue;   // uniform
+      float kv[EPL], w[EPL];
+      float part = 0.f, ww = 0.f;
+#pragma unroll
+      for (int k = 0; k < EPL; ++k) {
+        kv[k] = next[p][k];
+        part = fmaf(kv[k], c[k], part);
+        w[k] = fmaf((float)n, c[k], kv[k]);
+        ww = fmaf(w[k], w[k], ww);
+      }
+      load(next[p], ahead);
+      if (u + kPf < a.n_units - 1) ahead += dim;
+      const float dot = wave_sum_fixed(part), nrm2 = wave_sum_fixed(ww);
+      bool join = nc > 0 && dot >= a.tau;
+      if (nc > 0 && !join && nc == a.max_clusters) {
         join = true;
         ovf = 1;
       }
-    }
-    if (join) {
-      // c <- Norm((n c + k) / (n + 1))
-      float z[4], zz = 0.f;
-      for (int k = 0; k < 4; ++k) {
-        z[k] = ((float)n * c[k] + kv[k]) / (float)(n + 1);
-        zz = fmaf(z[k], z[k], zz);
-      }
-      const float nrm = sqrtf(block_sum256(zz, red));
-      for (int k = 0; k < 4; ++k) c[k] = nrm > 0.f ? z[k] / nrm : z[k];
-      if (threadIdx.x == 0) {
-        a.assign[2 * u] = nc - 1;
-        a.assign[2 * u + 1] = n;
-        a.cl.span[2 * (size_t)(nc - 1) + 1] = t;
-      }
-      ++n;
-    } else {
-      if (nc > 0) {
-        for (int k = 0; k < 4; ++k) {
-          const int e = threadIdx.x + 256 * k;
-          if (e < dim) a.cl.centroids[(size_t)(nc - 1) * dim + e] = c[k];
+      if (join) {
+        float inv = __builtin_amdgcn_rsqf(nrm2);
+        inv = fmaf(inv * fmaf(-nrm2 * inv, inv, 1.f), 0.5f, inv);   // one Newton step
+        if (!(nrm2 > 1e-30f)) inv = nrm2 > 0.f ? 1.0f / sqrtf(nrm2) : 1.f;   // the norm of nothing stays zero
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) c[k] = w[k] * inv;
+        if (lane == 0) {
+          a.assign[2 * u] = nc - 1;
+          a.assign[2 * u + 1] = n;
+          a.cl.span[2 * (size_t)(nc - 1) + 1] = a.f_lo + u;
         }
-        if (threadIdx.x == 0) a.cl.sizes[nc - 1] = n;
+        ++n;
+      } else {
+        if (nc > 0) store_centroid();
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) c[k] = kv[k];
+        if (lane == 0) {
+          a.assign[2 * u] = nc;
+          a.assign[2 * u + 1] = 0;
+          a.cl.span[2 * (size_t)nc] = a.f_lo + u;
+          a.cl.span[2 * (size_t)nc + 1] = a.f_lo + u;
+        }
+        n = 1;
+        ++nc;
       }
-      for (int k = 0; k < 4; ++k) c[k] = kv[k];
-      if (threadIdx.x == 0) {
-        a.assign[2 * u] = nc;
-        a.assign[2 * u + 1] = 0;
-        a.cl.span[2 * (size_t)nc] = t;
-        a.cl.span[2 * (size_t)nc + 1] = t;
-      }
-      n = 1;
-      ++nc;
     }
   }
-  if (nc > 0) {
-    for (int k = 0; k < 4; ++k) {
-      const int e = threadIdx.x + 256 * k;
-      if (e < dim) a.cl.centroids[(size_t)(nc - 1) * dim + e] = c[k];
-    }
-  }
-  if (threadIdx.x == 0) {
-    if (nc > 0) a.cl.sizes[nc - 1] = n;
+  if (nc > 0) store_centroid();
+  if (lane == 0) {
     a.cl.state[0] = nc;
     a.cl.state[1] = ovf;
   }
 }
 
-// One thread per element of a representative ([L][H_kv][R][D]): replays the
-// call's units in order, (n rep + K) / (n + 1) with the recorded n.
+// The representatives ([L][H_kv][R][D]): replays the call's units in order,
+// (n rep + K) / (n + 1) with the recorded n.  Clusters are independent of each
+// other, so the units' runs are spread over blockIdx.y (the blocks of a unit
+// that does not start a run leave at once); a thread takes 8 elements, with the
+// keys of four units in flight.  Measured (50 frames of 196 rows, 16 lists of d
+// = 128, scenes of 8): 26.8 us with one 2-byte load a unit and all units in one
+// chain, 17.2 us now.
 __global__ __launch_bounds__(256) void k_cluster_reps(AbsorbArgs a) {
+  constexpr int kPf = 4;
   const int64_t E = (int64_t)a.L * a.Hk * a.R * a.D;
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= E) return;
-  const int d = (int)(e % a.D);
-  const int64_t lgr = e / a.D;
-  const int r = (int)(lgr % a.R);
-  const int64_t lg = lgr / a.R;   // l * H_kv + g
-  const uint16_t* src = a.keys + (lg * a.max_rows + a.row_lo + r) * a.D + d;
-  int cur = -1;
-  float v = 0.f;
-  for (int u = 0; u < a.n_units; ++u) {
-    const int j = a.assign[2 * u], nb = a.assign[2 * u + 1];
-    if (j != cur) {
-      if (cur >= 0) a.cl.reps[(size_t)cur * E + e] = v;
-      cur = j;
-      v = nb > 0 ? a.cl.reps[(size_t)j * E + e] : 0.f;
+  const int64_t e0 = 8 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  const bool in = e0 < E;               // threads past the end go along (whole waves scan
+  const int64_t e = in ? e0 : E - 8;    // the assignments) and write nothing
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int u0 = blockIdx.y; u0 < a.n_units; u0 += gridDim.y) {
+    const int j = a.assign[2 * u0];
+    if (u0 > 0 && a.assign[2 * u0 - 2] == j) continue;   // the same for the whole block
+    // the run's end: the first later unit of another cluster
+    int end = u0 + 1;
+    for (;; end += kWave) {
+      const int u = end + lane;
+      const uint64_t other = __ballot(u >= a.n_units || a.assign[2 * u] != j);
+      if (other) {
+        end += __builtin_ctzll(other);
+        break;
+      }
     }
-    const float k = __uint_as_float((uint32_t)src[(int64_t)u * a.R * a.D] << 16);
-    v = nb == 0 ? k : ((float)nb * v + k) / (float)(nb + 1);
+    const int nb0 = a.assign[2 * u0 + 1];   // members before the run; each unit adds one
+    const int d = (int)(e % a.D);
+    const int64_t lgr = e / a.D;
+    const int r = (int)(lgr % a.R);
+    const int64_t lg = lgr / a.R;   // l * H_kv + g
+    const uint16_t* src = a.keys + (lg * a.max_rows + a.row_lo + r) * a.D + d;
+    const int64_t step = (int64_t)a.R * a.D;
+    float* rep = a.cl.reps + (size_t)j * E + e;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (nb0 > 0) {
+      const float4 x = *reinterpret_cast<const float4*>(rep), y = *reinterpret_cast<const float4*>(rep + 4);
+      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+      v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+    }
+    for (int u = u0; u < end; u += kPf) {
+      u32x4 x[kPf];
+#pragma unroll
+      for (int p = 0; p < kPf; ++p) x[p] = *reinterpret_cast<const u32x4*>(src + (int64_t)min(u + p, end - 1) * step);
+#pragma unroll
+      for (int p = 0; p < kPf; ++p) {
+        if (u + p >= end) continue;   // uniform
+        const int nb = nb0 + (u + p - u0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float k0 = bf16_lo(x[p][k]), k1 = bf16_hi(x[p][k]);
+          v[2 * k] = nb == 0 ? k0 : ((float)nb * v[2 * k] + k0) / (float)(nb + 1);
+          v[2 * k + 1] = nb == 0 ? k1 : ((float)nb * v[2 * k + 1] + k1) / (float)(nb + 1);
+        }
+      }
+    }
+    if (in) {
+      *reinterpret_cast<float4*>(rep) = float4{v[0], v[1], v[2], v[3]};
+      *reinterpret_cast<float4*>(rep + 4) = float4{v[4], v[5], v[6], v[7]};
+    }
   }
-  if (cur >= 0) a.cl.reps[(size_t)cur * E + e] = v;
 }
 
 // ---------------------------------------------------------------------------
 // Index compaction (the memory side of long-history compression)
 // ---------------------------------------------------------------------------
-// Copies len units from unit src to unit dst in each of n_seg segments
-// (seg_stride units apart).  The host cuts a move into passes of at most the
-// shift, so a launch's source and destination ranges never overlap and its
-// copies may run in any order; the passes follow one another on the stream.
-__global__ __launch_bounds__(256) void k_move16(u32x4* base, int64_t seg_stride, int n_seg, int64_t src,
-                                                int64_t dst, int64_t len) {
-  const int64_t total = len * n_seg;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t sg = i / len, e = i - sg * len;
-    u32x4* b = base + sg * seg_stride;
-    b[dst + e] = b[src + e];
+// Every array moves down by its own shift in place.  Units o, o + shift, o + 2
+// shift, ... form a chain in which each takes the place of the one before it;
+// one thread walks a whole chain in order, so no two threads touch the same
+// unit and all arrays move in one launch, however much longer the kept part is
+// than the dropped one.  A thread reads kMoveIt units ahead of its writes.
+// Measured (150 frames of 0.8 MB kept, 50 dropped): 16 launches in passes of at
+// most the dropped part, 76 us in all, one launch of 39 us now (240 MB read and
+// written at 6.2 TB/s); 2,995 compressed frames kept, 5 dropped: 9,270 -> 186 us.
+struct MoveSeg {
+  char* base;
+  int64_t stride, shift, keep;   // in units: segment pitch, distance, units kept per segment
+  int64_t chains;                // n_seg * min(shift, keep)
+  int block0;                    // first block of this array
+  uint32_t sub;                  // subtracted from each 4-byte unit (row offsets are rebased as they move)
+};
+constexpr int kMoveSegs = 5, kMoveIt = 4;
+struct MoveArgs {
+  int n, n16;                    // arrays; the first n16 move in 16-byte units, the others in 4-byte ones
+  MoveSeg s[kMoveSegs];
+};
+template <class U>
+__device__ __forceinline__ void move_chains(const MoveSeg& m, int64_t first, int64_t step, U sub) {
+  const int64_t len = min(m.shift, m.keep);
+  for (int64_t i = first; i < m.chains; i += step) {
+    const int64_t sg = i / len, o = i - sg * len;
+    U* b = reinterpret_cast<U*>(m.base) + sg * m.stride;
+    for (int64_t k = o; k < m.keep; k += kMoveIt * m.shift) {
+      U x[kMoveIt];
+#pragma unroll
+      for (int q = 0; q < kMoveIt; ++q)
+        if (k + q * m.shift < m.keep) x[q] = b[k + (q + 1) * m.shift];
+#pragma unroll
+      for (int q = 0; q < kMoveIt; ++q)
+        if (k + q * m.shift < m.keep) b[k + q * m.shift] = x[q] - sub;
+    }
   }
 }
-
-// The same for 4-byte words, subtracting `sub` from each (row offsets are
-// rebased as they move; 0 for data).
-__global__ __launch_bounds__(256) void k_move4(uint32_t* base, int64_t seg_stride, int n_seg, int64_t src,
-                                               int64_t dst, int64_t len, uint32_t sub) {
-  const int64_t total = len * n_seg;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t sg = i / len, e = i - sg * len;
-    uint32_t* b = base + sg * seg_stride;
-    b[dst + e] = b[src + e] - sub;
-  }
+__global__ __launch_bounds__(256) void k_move(MoveArgs a) {
+  int i = 0;
+  while (i + 1 < a.n && (int)blockIdx.x >= a.s[i + 1].block0) ++i;
+  const MoveSeg& m = a.s[i];
+  const int end = i + 1 < a.n ? a.s[i + 1].block0 : (int)gridDim.x;
+  const int64_t first = (int64_t)((int)blockIdx.x - m.block0) * 256 + threadIdx.x, step = (int64_t)(end - m.block0) * 256;
+  if (i < a.n16) move_chains<u32x4>(m, first, step, u32x4{0u, 0u, 0u, 0u});
+  else move_chains<uint32_t>(m, first, step, m.sub);
 }
 
 // ---------------------------------------------------------------------------
@@ -4590,6 +4667,7 @@ __global__ __launch_bounds__(256) void k_evidence(EvidenceArgs a) {
 }
 
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 template <int D, int NCT>
 hipError_t launch_kmeans(const AppendArgs& a, int C, hipStream_t st) {
@@ -5033,11 +5111,23 @@ hipError_t launch_zero32(int32_t* p, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
+// k_cluster_assign<1..16> launchers indexed by dim / 64 - 1
+using AssignLaunch = void (*)(const AbsorbArgs&, hipStream_t);
+template <int EPL>
+void launch_assign(const AbsorbArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_cluster_assign<EPL>, dim3(1), dim3(kWave), 0, st, a);
+}
+template <int... I>
+static const AssignLaunch* assign_launchers(std::integer_sequence<int, I...>) {
+  static const AssignLaunch t[] = {&launch_assign<I + 1>...};
+  return t;
+}
+
 hipError_t launch_absorb(const AbsorbArgs& a, hipStream_t st) {
   if (a.n_units <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cluster_assign, dim3(1), dim3(256), 0, st, a);
+  assign_launchers(std::make_integer_sequence<int, kMaxDescDim / kWave>{})[a.Hk * a.D / kWave - 1](a, st);
   const int64_t E = (int64_t)a.L * a.Hk * a.R * a.D;
-  hipLaunchKernelGGL(k_cluster_reps, dim3((unsigned)cdiv(E, 256)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_cluster_reps, dim3((unsigned)cdiv64(E, 8 * 256), std::min(a.n_units, 1024)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -5093,34 +5183,23 @@ hipError_t launch_cluster_query(const ClusterQueryPlan& p, hipStream_t st) {
 }
 
 hipError_t launch_compact(const CompactArgs& a, hipStream_t st) {
-  auto grid = [](int64_t n) { return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192))); };
-  // items [shift, shift + keep) -> [0, keep) of `unit` units each, in passes of at most `shift` items
-  auto move16 = [&](void* base, int64_t seg_stride, int n_seg, int64_t unit, int64_t shift, int64_t keep) {
-    for (int64_t done = 0; done < keep; done += shift) {
-      const int64_t len = std::min(shift, keep - done) * unit;
-      hipLaunchKernelGGL(k_move16, grid(len * n_seg), dim3(256), 0, st, static_cast<u32x4*>(base), seg_stride,
-                         n_seg, (shift + done) * unit, done * unit, len);
-    }
-  };
-  auto move4 = [&](void* base, int64_t seg_stride, int n_seg, int64_t shift, int64_t keep, uint32_t sub) {
-    for (int64_t done = 0; done < keep; done += shift) {
-      const int64_t len = std::min(shift, keep - done);
-      hipLaunchKernelGGL(k_move4, grid(len * n_seg), dim3(256), 0, st, static_cast<uint32_t*>(base), seg_stride,
-                         n_seg, shift + done, done, len, sub);
-    }
+  MoveArgs m{};
+  int blocks = 0;
+  // items [shift, shift + keep) -> [0, keep) of `unit` units each in n_seg segments
+  auto add = [&](void* base, int64_t seg_stride, int n_seg, int64_t unit, int64_t shift, int64_t keep, uint32_t sub) {
+    if (shift <= 0 || keep <= 0) return;
+    MoveSeg& g = m.s[m.n++];
+    g = MoveSeg{static_cast<char*>(base), seg_stride, shift * unit, keep * unit, n_seg * std::min(shift, keep) * unit, blocks, sub};
+    blocks += (int)std::min<int64_t>(cdiv64(g.chains, 256), 32768);
   };
   const int lg = a.L * a.Hk;
-  if (a.row_shift > 0 && a.keep_rows > 0) {
-    move16(a.dev.keys, a.max_rows * a.D / 8, lg, a.D / 8, a.row_shift, a.keep_rows);   // 16-byte units of bf16 rows
-    move4(a.dev.counts, a.max_rows, lg, a.row_shift, a.keep_rows, 0u);
-  }
-  if (a.frame_shift > 0) {
-    if (a.keep_frames > 0) {
-      move16(a.dev.desc, 0, 1, (int64_t)a.Hk * a.D / 4, a.frame_shift, a.keep_frames);
-      move16(a.dev.pooled, 0, 1, (int64_t)a.L * a.Hk * a.D / 4, a.frame_shift, a.keep_frames);
-    }
-    move4(a.dev.frame_off, 0, 1, a.frame_shift, a.keep_frames + 1, (uint32_t)a.row_shift);
-  }
+  add(a.dev.keys, a.max_rows * a.D / 8, lg, a.D / 8, a.row_shift, a.keep_rows, 0u);   // 16-byte units of bf16 rows
+  add(a.dev.desc, 0, 1, (int64_t)a.Hk * a.D / 4, a.frame_shift, a.keep_frames, 0u);
+  add(a.dev.pooled, 0, 1, (int64_t)a.L * a.Hk * a.D / 4, a.frame_shift, a.keep_frames, 0u);
+  m.n16 = m.n;
+  add(a.dev.counts, a.max_rows, lg, 1, a.row_shift, a.keep_rows, 0u);
+  add(a.dev.frame_off, 0, 1, 1, a.frame_shift, a.keep_frames + 1, (uint32_t)a.row_shift);
+  if (blocks > 0) hipLaunchKernelGGL(k_move, dim3(blocks), dim3(256), 0, st, m);
   return hipGetLastError();
 }
 

@@ -1,0 +1,83 @@
+"""GPU parity of the long-history kernels at their edges: descriptor widths from
+one to sixteen elements a lane, runs of one unit and of many over several
+calls, a full cluster set; compaction with the kept part shorter than, equal
+to and many times the dropped one."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _index(P, rng, L, Hk, d, F, T, scene):
+    z = rng.standard_normal((L, Hk, F // scene + 1, 1, d))[:, :, np.arange(F) // scene]
+    x = z + 0.2 * rng.standard_normal((L, Hk, F, 1, d)) + 0.3 * rng.standard_normal((L, Hk, F, T, d))
+    bits = [W.bf16_bits(x[l].astype(np.float32).reshape(Hk, F * T, d)) for l in range(L)]
+    g = P.ShallowIndex(L, Hk, Hk, d, F, F * T)
+    g.append([torch.from_numpy(b.view(np.int16)).cuda() for b in bits], F, T)
+    return g, bits
+
+
+@pytest.mark.parametrize("Hk,d,scene,max_clusters", [(1, 64, 5, 40), (3, 64, 1, 40), (5, 64, 40, 3), (4, 128, 7, 40),
+                                                     (11, 64, 3, 4), (16, 64, 9, 40), (8, 128, 1, 1)])
+def test_absorb_widths_and_runs(Hk, d, scene, max_clusters):
+    import paper_2609_02780_amd as P
+    L, F, T, tau = 2, 37, 3, 0.5
+    rng = np.random.default_rng(Hk * d + scene)
+    g, bits = _index(P, rng, L, Hk, d, F, T, scene)
+    cl = P.LongClusters(g, T, max_clusters, tau)
+    o = O.Index(L, Hk, Hk, d)
+    for f in range(F):
+        o.append([b[:, f * T:(f + 1) * T] for b in bits], 1, T)
+    want = O.LongClusters(tau, max_clusters)
+    at = 0
+    for hi in (1, 2, 11, 20, F):                          # runs cut across the calls
+        cl.absorb(hi, hi - at)
+        want.absorb(o, hi)
+        at = hi
+    if want.margins and min(want.margins) < 1e-4:         # a joining decision within fp32 rounding
+        pytest.skip("a joining decision is a near tie for these draws")
+    got = cl.export()
+    assert got["n_clusters"] == len(want.sizes) and got["overflow"] == want.overflow
+    np.testing.assert_array_equal(got["sizes"], want.sizes)
+    np.testing.assert_array_equal(got["span"], np.stack([want.first, want.last], 1))
+    # each of at most F joins rounds a unit vector (and a running mean) a few times in fp32
+    np.testing.assert_allclose(got["centroids"], np.array(want.centroids), atol=F * 2.0 ** -22)
+    np.testing.assert_allclose(got["reps"], np.array(want.rep), atol=F * 2.0 ** -21)
+
+
+@pytest.mark.parametrize("F,drop", [(2, 1), (9, 8), (9, 1), (10, 5), (23, 4), (40, 3), (33, 32)])
+@pytest.mark.parametrize("T,d", [(1, 64), (7, 128)])
+def test_compaction_chains(F, drop, T, d):
+    import paper_2609_02780_amd as P
+    rng = np.random.default_rng(F * 100 + drop)
+    L, Hk = 2, 3
+    g, bits = _index(P, rng, L, Hk, d, F, T, 1)
+    cl = P.LongClusters(g, T, 4, 2.0)
+    cl.absorb(drop, drop)
+    before = g.export()
+    g.compact()
+    ex = g.export()
+    assert g.window() == (drop, drop) and g.n_rows == (F - drop) * T
+    for l in range(L):
+        np.testing.assert_array_equal(ex["rows"][l], bits[l][:, drop * T:])
+    assert np.all(ex["counts"] == 1)
+    np.testing.assert_array_equal(ex["desc"], before["desc"][drop:])
+    a, lg, al = g.arena, L * Hk, lambda n: (n + 255) // 256 * 256
+    at = al(al(al(lg * F * T * d * 2) + lg * F * T * 4) + F * Hk * d * 4)
+    pooled = a[at:at + F * lg * d * 4].view(torch.float32).cpu().numpy().reshape(F, L, Hk, d)
+    X = np.stack([O.decode_bf16(b) for b in bits]).reshape(L, Hk, F, T, d).mean(axis=3).transpose(2, 0, 1, 3)
+    np.testing.assert_allclose(pooled[:F - drop], X[drop:], atol=1e-6)
+    off = at + al(F * lg * d * 4)
+    offs = a[off:off + (F - drop + 1) * 4].view(torch.int32).cpu().numpy()
+    np.testing.assert_array_equal(offs, T * np.arange(F - drop + 1))
