@@ -196,7 +196,10 @@ ss_status ss_index_append(ss_index* idx, const void* const* layer_keys, int32_t 
                           int64_t* first_frame_id);
 
 /* Workspace bytes ss_retrieve needs for this batch in the indices' current state
- * (0 if the arguments are invalid).  n_q: host array of n_streams token counts. */
+ * (0 if the arguments are invalid).  n_q: host array of n_streams token counts.
+ * Short lists (head_mode 0, at most 32,768 candidate rows) are sized for the
+ * score of every row; ss_retrieve takes a workspace without room for those all
+ * the same, on the route of longer lists. */
 size_t ss_retrieve_workspace_bytes(ss_index* const* idx, int32_t n_streams, const int32_t* n_q,
                                    const ss_retrieve_params* params);
 
@@ -258,7 +261,10 @@ ss_status ss_retrieve_noalloc(ss_index* const* idx, int32_t n_streams, const voi
  *   pool        int32 [n_streams][pool_mult*n_select] the vote-ranked pool, -1 padded;
  *   pool_n      int32 [n_streams];
  *   list_stats  int32 [n_streams][n_lists][2]: candidates kept by the streaming
- *               pass, and 1 if the list took the exact fallback path. */
+ *               pass, and 1 if the list took the exact fallback path.  Lists
+ *               short enough to be selected from every row's score have neither:
+ *               the rows at or above the k-th score, and 1 if those exceed the
+ *               candidate capacity. */
 typedef struct {
   int32_t* topk_pos;
   float* topk_score;

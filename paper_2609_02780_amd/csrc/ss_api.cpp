@@ -257,9 +257,10 @@ ss_status check_params(const ss_retrieve_params* p, int Hk, int D) {
 }
 
 // Builds the plan of streams [s0, s0 + S) of a validated batch (`queries` may be
-// NULL when only the workspace size is wanted).
+// NULL when only the workspace size is wanted).  all_rows: take the route of
+// short lists where the batch has none longer than kAllRows.
 void build_plan(ss::RetrievePlan& p, ss_index* const* idx, int s0, int S, const void* const* queries,
-                const int32_t* n_q, const ss_retrieve_params* prm) {
+                const int32_t* n_q, const ss_retrieve_params* prm, bool all_rows) {
   std::memset(&p, 0, sizeof p);
   const ss_index_desc& d = idx[0]->desc;
   p.S = S;
@@ -317,6 +318,19 @@ void build_plan(ss::RetrievePlan& p, ss_index* const* idx, int s0, int S, const 
   }
   p.f_max = std::max(p.f_max, 1);
   p.m_max = std::max(p.m_max, 1);
+  // Short lists: score and keep every row instead of sampling, streaming the
+  // candidates and reading the keys twice.  What it costs is writing and reading
+  // the scores, so beyond 8,192 rows a batch takes it up to 3 M of them.
+  // Per call, sampled / all rows, k = 64, d = 128: 112 lists of 2,048 rows 59.4 /
+  // 30.6 us, 8,192 rows 45.4 / 37.5, 19,200 rows 51.8 / 47.5; 160 lists (8 KV
+  // heads) of 16,384 rows 66.7 / 64.0, of 25,600 (4.1 M) 81.2 / 84.0; 448 lists of
+  // 8,192 rows 84 / 65, of 19,200 107 / 110.
+  const int64_t lists = (int64_t)p.S * p.NL;
+  if (all_rows && prm->head_mode == 0 && prm->top_k <= ss::kAllTopK && n_max <= ss::kAllRows && p.S * p.L <= 128 &&
+      lists <= 512 && (n_max <= 8192 || lists * n_max <= 3'000'000)) {
+    p.all_rows = true;
+    p.m_max = (int)((std::max<int64_t>(n_max, 1) + 15) / 16 * 16);   // whole tiles
+  }
   p.cap = (int)candidate_cap(prm->top_k, n_max);
   p.dbg_hist_stride = hist;
 }
@@ -337,18 +351,22 @@ ss_status check_batch(ss_index* const* idx, int32_t n_streams, const int32_t* n_
 }
 
 size_t group_ws(ss_index* const* idx, int s0, int S, const int32_t* n_q,
-                const ss_retrieve_params* prm) {
+                const ss_retrieve_params* prm, bool all_rows) {
   ss::RetrievePlan p;
-  build_plan(p, idx, s0, S, nullptr, n_q, prm);
+  build_plan(p, idx, s0, S, nullptr, n_q, prm, all_rows);
   return ss::carve_workspace(p, nullptr);
 }
 
+// The workspace a batch should have (every group on its preferred route), or the
+// one it can do with (`least`: the smaller of each group's two routes).
 size_t batch_ws(ss_index* const* idx, int32_t n_streams, const int32_t* n_q,
-                const ss_retrieve_params* prm) {
+                const ss_retrieve_params* prm, bool least) {
   size_t need = 0;
   for (int s0 = 0; s0 < n_streams; s0 += ss::kMaxStreams) {
     const int S = std::min(ss::kMaxStreams, n_streams - s0);
-    need = std::max(need, group_ws(idx, s0, S, n_q, prm));
+    size_t g = group_ws(idx, s0, S, n_q, prm, true);
+    if (least || g > ss::kNoAllocBytes) g = std::min(g, group_ws(idx, s0, S, n_q, prm, false));
+    need = std::max(need, g);
   }
   return need;
 }
@@ -368,7 +386,7 @@ ss_status retrieve_common(ss_index* const* idx, int32_t n_streams, const void* c
   if (!frame_ids || !votes || !mass || !n_out)
     return fail(SS_ERR_INVALID_ARGUMENT, "an output pointer is NULL");
   if (!ws || !aligned(ws, 256)) return fail(SS_ERR_WORKSPACE, "workspace NULL or not 256-byte aligned");
-  const size_t need = batch_ws(idx, n_streams, n_q, prm);
+  const size_t need = batch_ws(idx, n_streams, n_q, prm, true);
   if (ws_bytes < need)
     return fail(SS_ERR_WORKSPACE, "workspace %zu bytes, %zu needed", ws_bytes, need);
   if (dbg && dbg->topk_score == nullptr && dbg->topk_pos != nullptr)
@@ -379,7 +397,9 @@ ss_status retrieve_common(ss_index* const* idx, int32_t n_streams, const void* c
   for (int s0 = 0; s0 < n_streams; s0 += ss::kMaxStreams) {
     const int S = std::min(ss::kMaxStreams, n_streams - s0);
     ss::RetrievePlan p;
-    build_plan(p, idx, s0, S, queries, n_q, prm);
+    build_plan(p, idx, s0, S, queries, n_q, prm, true);
+    // a workspace too small for the short lists' route may still do for the other
+    if (p.all_rows && ss::carve_workspace(p, nullptr) > ws_bytes) build_plan(p, idx, s0, S, queries, n_q, prm, false);
     ss::carve_workspace(p, ws);
     p.out_ids = frame_ids + (size_t)s0 * prm->n_select;
     p.out_votes = votes + (size_t)s0 * prm->n_select;
@@ -941,7 +961,7 @@ ss_status ss_index_append(ss_index* idx, const void* const* layer_keys, int32_t 
 size_t ss_retrieve_workspace_bytes(ss_index* const* idx, int32_t n_streams, const int32_t* n_q,
                                    const ss_retrieve_params* params) {
   if (check_batch(idx, n_streams, n_q, params) != SS_OK) return 0;
-  return batch_ws(idx, n_streams, n_q, params);
+  return batch_ws(idx, n_streams, n_q, params, false);
 }
 
 ss_status ss_retrieve(ss_index* const* idx, int32_t n_streams, const void* const* queries,
@@ -960,7 +980,7 @@ ss_status ss_retrieve_noalloc(ss_index* const* idx, int32_t n_streams, const voi
   return guarded([&]() -> ss_status {
     ss_status st = check_batch(idx, n_streams, n_q, params);
     if (st) return st;
-    const size_t need = batch_ws(idx, n_streams, n_q, params);
+    const size_t need = batch_ws(idx, n_streams, n_q, params, true);
     if (need > ss::kNoAllocBytes)
       return fail(SS_ERR_WORKSPACE,
                   "this batch needs a %zu-byte workspace, above the %zu bytes of the library-owned one: "

@@ -21,6 +21,8 @@ constexpr int kMaxTokensCompress = 256;
 constexpr int kMaxCentroids = 64;
 constexpr int kMaxLayers = 32;
 constexpr int kMaxListsPerStream = 4096;  // n_layers * n_q_heads
+constexpr int kAllRows = 32768;      // longest list selected from all its scores (32 per thread of 1,024)
+constexpr int kAllTopK = 1024;       // and the largest k of that route
 
 // The host-side RetrievePlan is never passed to a kernel as a whole; each
 // kernel receives a compact argument struct built from it.
@@ -87,6 +89,7 @@ struct RetrievePlan {
   int top_k, n_select, pool, pool_mult;
   int cap;               // candidate capacity per list
   int k_max;             // max over streams of kk
+  bool all_rows;         // short lists (head_mode 0): every row's score is kept and selected from
   int m_max, f_max;
   int chunk_rows, samp_chunk;
   StreamPlan st[kMaxStreams];

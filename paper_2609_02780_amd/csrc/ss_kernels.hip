@@ -27,6 +27,9 @@
 //               and selects exactly from them instead.  Each list then adds its
 //               selected rows up per frame (count, fixed-point score sum).
 //               k_select_dense runs two blocks per CU for many lists.
+//   k_score_all, k_select_all  short lists (head mode 0): prep and every row's
+//               score in one launch, then the exact top-k from all scores, in
+//               the place of sample, cut-off, stream and k_select.
 //   k_votes_pool  per stream, the vote-ranked pool from the frames' votes and
 //               fixed-point attention mass: a vote histogram fixes the cut,
 //               frames tied at it are ranked by counting (a radix cut over the
@@ -446,7 +449,7 @@ constexpr int kPrepGroups = 4;
 // token group 0 (the first 2 D threads, whole waves) hold the result: they
 // write it to `out_lds` if given, and to the global B tile and the column L1
 // norms if `global` is set.
-template <int D>
+template <int D, int DEPTH = 16>
 __device__ __forceinline__ void prep_b(const PrepArgs& a, int pair_local, int g,
                                        float (*part)[2 * D][8], u32x4* out_lds, bool global) {
   constexpr int KS = D / 32, NE = D / 8, NT = 2 * D;  // NT threads per token group
@@ -469,15 +472,15 @@ __device__ __forceinline__ void prep_b(const PrepArgs& a, int pair_local, int g,
   const int e0 = 8 * ec;
   for (int h = h0; h < h1; ++h) {
     const uint16_t* qh = q + (size_t)h * nq * D + e0;
-    // tokens tg, tg + 4, ... in increasing order; 16 loads in flight per pass,
+    // tokens tg, tg + 4, ... in increasing order; DEPTH loads in flight per pass,
     // from clamped in-bounds token indices (only tokens below nq are added)
-    for (int j0 = tg; j0 < nq; j0 += 16 * kPrepGroups) {
-      u32x4 v[16];
+    for (int j0 = tg; j0 < nq; j0 += DEPTH * kPrepGroups) {
+      u32x4 v[DEPTH];
 #pragma unroll
-      for (int u = 0; u < 16; ++u)
+      for (int u = 0; u < DEPTH; ++u)
         v[u] = *reinterpret_cast<const u32x4*>(qh + (size_t)min(j0 + u * kPrepGroups, nq - 1) * D);
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
+      for (int u = 0; u < DEPTH; ++u) {
         if (j0 + u * kPrepGroups < nq) {
 #pragma unroll
           for (int w = 0; w < 4; ++w) {
@@ -1239,6 +1242,108 @@ __global__ __launch_bounds__(8 * D) void k_prep_sample(PrepArgs pa, ScoreArgs a,
   for (int i = threadIdx.x; i < a.G * kPsTiles * kTile; i += blockDim.x) {
     const int c = i / (kPsTiles * kTile), u = i - c * (kPsTiles * kTile);
     if (u < nu) a.samp[(size_t)(list0 + c) * a.samp_stride + u0 + u] = sout[c][u];
+  }
+}
+
+// Query prep and the scores of every row in one launch (head-mode 0, short
+// lists): block (group, slice) forms the group's B tile as k_prep does and scores
+// its slice of the group's tiles with the streaming pass's arithmetic and loads
+// (whole tiles, 1 KiB an instruction), writing each list's scores for k_select_all.
+// Where every row's score is kept there is no sample, no cut-off, no candidate
+// buffer and no second read of the keys.  The blocks also clear their stream's
+// frame accumulators.  The first tiles' loads go out before the
+// query prep, whose round trips they need not wait for.  Measured (112 lists of
+// 19,200 rows, d = 128, 32 query tokens): prep, cut-off and stream 13.0 + 18.9 us
+// with their boundary, 20.8 us here (the prep ends at 10.4 us behind the loads
+// already in flight, the pass at 18); 8 lists of 1,024 rows 8.7 + 5.0 + 14.8 us,
+// 6.5 us here.
+struct AllArgs {
+  int blk_base[kMaxStreams + 1];   // first block of each stream
+  int spg[kMaxStreams];            // blocks (slices) per (layer, KV head) group of each stream
+  int f[kMaxStreams];              // candidate frames
+  int f_max;
+  int32_t* votes_g;
+  int64_t* massfx_g;
+};
+
+template <int D>
+__global__ __launch_bounds__(8 * D) void k_score_all(PrepArgs pa, ScoreArgs a, AllArgs ps) {
+  constexpr int CPR = D / 8, TCH = 16 * CPR, NI = TCH / kWave, KS = D / 32;
+  constexpr int NW = 8 * D / kWave;   // waves per block
+  constexpr int PF = D == 128 ? 3 : 4;   // tiles in flight per wave
+  union AllShared {
+    float part[kPrepGroups][2 * D][8];
+    u32x4 tiles[NW][TCH];
+  };
+  __shared__ AllShared sh;
+  __shared__ u32x4 bsh[2 * KS * kWave];
+  int s = 0;
+  const int vb = blockIdx.x;
+  while (vb >= ps.blk_base[s + 1]) ++s;
+  const int rem = vb - ps.blk_base[s];
+  const int lg = rem / ps.spg[s], slice = rem - lg * ps.spg[s];
+  const int l = lg / a.Hk, g = lg - l * a.Hk;
+  {
+    int32_t* vg = ps.votes_g + (size_t)s * ps.f_max;
+    int64_t* mg = ps.massfx_g + (size_t)s * ps.f_max;
+    const int nt = (ps.blk_base[s + 1] - ps.blk_base[s]) * 8 * D;
+    for (int f = rem * 8 * D + threadIdx.x; f < ps.f[s]; f += nt) {
+      vg[f] = 0;
+      mg[f] = 0;
+    }
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, kg = lane >> 4, rl = lane & 15;
+  const int n = a.n[s], nt = a.ntile[s];
+  const int t0 = (int)((int64_t)slice * nt / ps.spg[s]), t1 = (int)((int64_t)(slice + 1) * nt / ps.spg[s]);
+  const uint16_t* seg = a.keys[s] + ((size_t)l * a.Hk + g) * (size_t)a.stride[s] * D;
+  // exactly n rows: the lanes past the last row, and tiles past the slice, read zeros
+  const __amdgpu_buffer_rsrc_t rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(seg), (short)0, n * D * 2, 0x00020000);
+  auto load = [&](int t, u32x4 (&V)[NI]) {
+    const uint32_t off = t < t1 ? (uint32_t)t * (TCH * 16) + lane * 16 : 0x80000000u;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) V[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + i * kWave * 16, 0, kAuxNT);
+  };
+  u32x4 V[PF][NI];
+#pragma unroll
+  for (int p = 0; p < PF; ++p) load(t0 + wave + NW * p, V[p]);
+  prep_b<D, 8>(pa, s * a.L + l, g, sh.part, bsh, slice == 0);   // (16 loads in flight would spill)
+  __syncthreads();   // the B tile is in LDS and the partial sums are read no more
+  u32x4* lt_ = sh.tiles[wave];
+  u32x4 bh[KS], bl[KS];
+#pragma unroll
+  for (int i = 0; i < KS; ++i) {
+    bh[i] = bsh[i * kWave + lane];
+    bl[i] = bsh[(KS + i) * kWave + lane];
+  }
+  const bool colv = col < a.G;
+  float* out = a.samp + (size_t)(s * a.NL + l * a.Hq + g * a.G + (colv ? col : 0)) * a.samp_stride + 4 * kg;
+  for (int t = t0 + wave; t < t1; t += NW * PF) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      const int tt = t + NW * p;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int q = i * kWave + lane, R = q >> 4, C = q & 15;
+        lt_[R * 16 + (C ^ (R & 15))] = V[p][i];
+      }
+      __builtin_amdgcn_wave_barrier();
+      load(tt + NW * PF, V[p]);
+      u32x4 A[KS];
+#pragma unroll
+      for (int i = 0; i < KS; ++i) {
+        const int q = rl * CPR + 4 * i + kg, R = q >> 4, C = q & 15;
+        A[i] = lt_[R * 16 + (C ^ (R & 15))];
+      }
+      __builtin_amdgcn_wave_barrier();
+      const f32x4 acc = score_hilo<KS>(A, bh, bl);
+      // whole tiles fit the stride (a multiple of 16); rows past n are not read
+      if (colv && tt < t1)
+        *reinterpret_cast<float4*>(out + (size_t)tt * kTile) =
+            float4{acc[0] + 0.0f, acc[1] + 0.0f, acc[2] + 0.0f, acc[3] + 0.0f};
+    }
   }
 }
 
@@ -2832,6 +2937,139 @@ __device__ void select_list(const ListArgs& a, int list, SelectShared& sh, uint3
     to_probabilities(sel, kk, lse);
   }
   finish_list(a, list, sel, kk, lv, lm);
+}
+
+// Exact top-k of a short list from the scores of all its rows (k_score_all), at
+// most N per thread, in registers.  Most rows are left out first: the k-th
+// largest of the threads' own maxima (k <= 1,024) is a bound that at least k rows
+// reach, one histogram round gives it to within a bin, and the few rows at or above it are selected from as the candidates of
+// longer lists are (or, where too many tie for that, all rows by radix).
+// Nothing can be missed, so there is no fallback; the debug counts are the rows
+// at or above the k-th value, and 1 where those exceed the candidate capacity of
+// longer lists.
+// Measured at 19,200 rows: 9.5 us (loads 2.7, bound and compaction 2.9, selection
+// 2.4), against about 17 us with radix rounds over all 32 slots a thread.
+constexpr int kAllKeep = 4096;   // rows kept by the bound (they take the place of the frame sums)
+template <int N>
+__global__ __launch_bounds__(1024) void k_select_all(ListArgs a) {
+  __shared__ SelectShared sh;
+  __shared__ uint32_t hist[kSelHist];
+  __shared__ uint32_t res[4];
+  __shared__ uint32_t ngather, nkeep;
+  __shared__ uint32_t mm[32];
+  __shared__ unsigned long long fx_sh;
+  static_assert(sizeof(sh.lm) >= kAllKeep * sizeof(uint64_t), "the kept keys fit the frame sums' place");
+  const int list = blockIdx.x, s = list / a.NL;
+  const int kk = a.kk[s], n = a.n[s];
+  uint64_t* sel = sh.sel;
+  if (kk == 0) {   // no rows: nothing is voted, the exponent only has to be finite
+    if (threadIdx.x == 0 && list == s * a.NL) a.sexp[s] = 0;
+    finish_list(a, list, sel, 0, sh.lv, sh.lm);
+    return;
+  }
+  // element 4 q + j of thread t is row 4 (t + 1024 q) + j
+  auto row_of = [&](int it) { return 4 * ((int)threadIdx.x + 1024 * (it >> 2)) + (it & 3); };
+  const float* v = a.samp + (size_t)list * a.samp_stride;
+  uint32_t u[N];
+#pragma unroll
+  for (int q = 0; q < N / 4; ++q) {
+    const float4 x = *reinterpret_cast<const float4*>(v + min(4 * ((int)threadIdx.x + 1024 * q), a.samp_stride - 4));
+    u[4 * q] = __float_as_uint(x.x);
+    u[4 * q + 1] = __float_as_uint(x.y);
+    u[4 * q + 2] = __float_as_uint(x.z);
+    u[4 * q + 3] = __float_as_uint(x.w);
+  }
+  if (threadIdx.x < kWave) {
+    const int xs = stream_exponent(a, s);
+    if (threadIdx.x == 0) {
+      list_mass_exponent() = xs;
+      if (list == s * a.NL) a.sexp[s] = xs;
+    }
+  }
+  if (threadIdx.x == 0) { ngather = 0; nkeep = 0; fx_sh = 0; }
+  for (int i = threadIdx.x; i < kSelHist; i += 1024) hist[i] = 0;
+  // rows past n take 0, below every score
+  uint32_t own = 0;
+#pragma unroll
+  for (int it = 0; it < N; ++it) {
+    u[it] = row_of(it) < n ? ord_u32(__uint_as_float(u[it])) : 0u;
+    own = max(own, u[it]);
+  }
+  uint32_t mn = own ? own : 0xFFFFFFFFu, mx = own;   // of the threads' maxima
+  block_minmax_u32(mn, mx, mm);
+  float lse = 0.f;
+  if (a.score_mode == 1) {
+    // the list's log-sum-exp over all its rows, in fixed point
+    const float M = ord_f32(mx);
+    unsigned long long part = 0;
+#pragma unroll
+    for (int it = 0; it < N; ++it)
+      if (u[it]) part += (unsigned long long)llrint(ldexp((double)__expf(ord_f32(u[it]) - M), kBelowExp));
+    part = wave_sum_u64(part);
+    if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&fx_sh, part);
+    __syncthreads();
+    lse = M + (float)log(ldexp((double)fx_sh, -kBelowExp));
+  }
+  // (n + 3) / 4 of the threads, at most all, hold rows: where those are fewer than
+  // k the list is short enough to keep all its rows
+  uint64_t* keep = reinterpret_cast<uint64_t*>(sh.lm);
+  uint32_t bound = 1u;
+  if (kk <= min(1024, (n + 3) / 4)) {
+    bound = mn;
+    if (mn < mx) {
+      uint32_t* wide = hist + 512;
+      const int bits = 32 - __clz(mx - mn), shift = bits > 11 ? bits - 11 : 0;
+      if (own) atomicAdd(&wide[pad32((own - mn) >> shift)], 1u);
+      __syncthreads();
+      find_digit_wide<32, true>(wide, (uint32_t)kk, res);
+      bound = mn + (res[0] << shift);
+    }
+  }
+#pragma unroll
+  for (int it = 0; it < N; ++it)
+    if (u[it] >= bound) {
+      const uint32_t slot = atomicAdd(&nkeep, 1u);
+      if (slot < (uint32_t)kAllKeep) keep[slot] = mk_key(u[it], (uint32_t)row_of(it));
+    }
+  __syncthreads();
+  const int kept = (int)nkeep;
+  if (kept <= kAllKeep) {
+    uint64_t key[4];
+#pragma unroll
+    for (int it = 0; it < 4; ++it) key[it] = keep[min((int)threadIdx.x + 1024 * it, kAllKeep - 1)];
+    select_from_keys<4>(key, kept, kk, sel, hist, res, ngather, mm);
+  } else {   // ties: radix over the key space, from all rows
+    __syncthreads();
+    const uint64_t cut = radix_select_u64(
+        [&](int i) { return mk_key(ord_u32(v[i]), (uint32_t)i); }, n, (uint32_t)kk, hist, res);
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < N; ++it) {
+      const uint64_t k = mk_key(u[it], (uint32_t)row_of(it));
+      if (u[it] && k >= cut) {
+        const uint32_t slot = atomicAdd(&ngather, 1u);
+        if (slot < (uint32_t)kMaxTopK) sel[slot] = k;
+      }
+    }
+  }
+  __syncthreads();
+  if (a.dbg_stats) {
+    uint32_t low = 0xFFFFFFFFu, top = 0;
+    for (int e = threadIdx.x; e < kk; e += 1024) low = min(low, (uint32_t)(sel[e] >> 32));
+    block_minmax_u32(low, top, mm);
+    if (threadIdx.x == 0) nkeep = 0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < N; ++it)
+      if (u[it] >= low) atomicAdd(&nkeep, 1u);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      a.dbg_stats[2 * list] = (int32_t)nkeep;
+      a.dbg_stats[2 * list + 1] = nkeep > (uint32_t)a.cap;
+    }
+  }
+  if (a.score_mode == 1) to_probabilities(sel, kk, lse);
+  finish_list(a, list, sel, kk, sh.lv, sh.lm);
 }
 
 // ---------------------------------------------------------------------------
@@ -4815,6 +5053,27 @@ hipError_t launch_stream_hp(const ScoreArgs& a, const RetrievePlan& p, int64_t t
   }
 }
 
+// Blocks of k_score_all: the tiles of all lists' groups in slices of equal size,
+// at least one slice a group and one tile a wave, at most one block a CU.
+int plan_all_blocks(const RetrievePlan& p, AllArgs& a) {
+  constexpr int kCus = 256;
+  int64_t tiles = 0;
+  for (int s = 0; s < p.S; ++s) tiles += (int64_t)p.L * p.Hk * cdiv(p.st[s].n, kTile);
+  int per = std::max(p.D / 8, cdiv(tiles, kCus)), blocks = 0;
+  for (;;) {
+    blocks = 0;
+    for (int s = 0; s < p.S; ++s) {
+      a.blk_base[s] = blocks;
+      a.spg[s] = std::max(1, cdiv(cdiv(p.st[s].n, kTile), per));
+      blocks += p.L * p.Hk * a.spg[s];
+    }
+    a.blk_base[p.S] = blocks;
+    if (blocks <= kCus || blocks == p.S * p.L * p.Hk) break;
+    per += (per + 3) / 4;
+  }
+  return blocks;
+}
+
 template <int D>
 hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
   // 1. query prep, fused with 2., the sample scores, in k_prep_sample (head
@@ -4843,9 +5102,12 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
   // one box: 10-minute index 110.9 -> 110.2 us per call, m = 1,072; compressed
   // 58.5 -> 56.3 us, m = 262) but not at the 1-hour index's 3,216 rows
   // (450.2 -> 456.3 us)
-  const bool pt = D == 128 && p.head_mode == 0 && !p.hm_prob && pairs <= 128 && lists <= cus && p.m_max <= 2048;
+  const bool all = p.all_rows;
+  AllArgs aa{};
+  const int all_blocks = all ? plan_all_blocks(p, aa) : 0;
+  const bool pt = !all && D == 128 && p.head_mode == 0 && !p.hm_prob && pairs <= 128 && lists <= cus && p.m_max <= 2048;
   ps.xcd_map = cus == 256 && ps_blocks % 8 == 0;
-  const bool fused = !pt && prep_hm == 0 && pairs <= 128 && ps_blocks <= cus;
+  const bool fused = !all && !pt && prep_hm == 0 && pairs <= 128 && ps_blocks <= cus;
   int nq_max = 0;
   for (int s = 0; s < p.S; ++s) nq_max = std::max(nq_max, p.st[s].nq);
   const bool hm_prep = prep_hm == 1 && pairs <= 128 && p.Hk <= 8 && p.G * nq_max <= kHmPrepTerms;
@@ -4861,7 +5123,7 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
     for (int s = 0; s < p.S; ++s) { a.nq[s] = p.st[s].nq; a.qscale[s] = p.st[s].qscale; }
     a.qB = reinterpret_cast<u32x4*>(p.qB);
     a.qcol = p.qcol;
-    if (fused || pt || hm_prep)
+    if (fused || pt || hm_prep || all)
       pa_fused = a;
     else
       hipLaunchKernelGGL(k_prep<D>, dim3(cnt * p.Hk), dim3(8 * D), 0, st, a);
@@ -4886,7 +5148,16 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
   la.below = p.below; la.lhat = p.lhat; la.cand_sc = p.cand_sc; la.left_max = p.left_max;
   la.cand_lse = p.cand_lse;
   // 2. sample scores, 3. thresholds
-  if (pt) {
+  if (all) {
+    // short lists: every row's score, then the selection from all of them
+    ScoreArgs a = make_score_args(p, K_STREAM);
+    aa.f_max = p.f_max;
+    aa.votes_g = p.votes;
+    aa.massfx_g = p.massfx;
+    for (int s = 0; s < p.S; ++s) aa.f[s] = p.st[s].f;
+    if (p.ev_start) (void)hipEventRecord(p.ev_start, st);
+    hipLaunchKernelGGL(k_score_all<D>, dim3(all_blocks), dim3(8 * D), 0, st, pa_fused, a, aa);
+  } else if (pt) {
     PtArgs t{};
     t.NL = p.NL; t.L = p.L; t.Hq = p.Hq; t.Hk = p.Hk; t.G = p.G; t.f_max = p.f_max;
     t.xcd_map = cus == 256 && lists % 8 == 0 && (lists / 8) % p.G == 0;
@@ -4932,12 +5203,13 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
     ListArgs lt = la;   // the cut-off over the estimated attention of the sample
     lt.samp = p.alpha;
     launch_thresh(lt, lists, p.m_max, false, st);
-  } else if (!pt) {
+  } else if (!pt && !all) {
     launch_thresh(la, lists, p.m_max, lists > 2 * cus, st);
   }
   // 4. streaming pass over every key row
-  if (p.ev_start) (void)hipEventRecord(p.ev_start, st);
-  if (p.head_mode == 0) {
+  if (p.ev_start && !all) (void)hipEventRecord(p.ev_start, st);
+  if (all) {
+  } else if (p.head_mode == 0) {
     ScoreArgs a = make_score_args(p, K_STREAM);
     a.score_mode = p.score_mode;
     a.below = p.below;
@@ -5006,7 +5278,12 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
     hipLaunchKernelGGL(k_cand_lse, dim3(lists * p.Hq), dim3(256), 0, st, la);
     hipLaunchKernelGGL(k_select_hp<D>, dim3(lists), dim3(1024), 0, st, la);
   }
-  else if (lists > 2 * cus) hipLaunchKernelGGL(k_select_dense<D>, dim3(lists), dim3(1024), 0, st, la);
+  else if (all) {
+    if (p.m_max <= 4096) hipLaunchKernelGGL(k_select_all<4>, dim3(lists), dim3(1024), 0, st, la);
+    else if (p.m_max <= 8192) hipLaunchKernelGGL(k_select_all<8>, dim3(lists), dim3(1024), 0, st, la);
+    else if (p.m_max <= 16384) hipLaunchKernelGGL(k_select_all<16>, dim3(lists), dim3(1024), 0, st, la);
+    else hipLaunchKernelGGL(k_select_all<32>, dim3(lists), dim3(1024), 0, st, la);
+  } else if (lists > 2 * cus) hipLaunchKernelGGL(k_select_dense<D>, dim3(lists), dim3(1024), 0, st, la);
   else hipLaunchKernelGGL(k_select<D>, dim3(lists), dim3(1024), 0, st, la);
   // 8. Gram matrix, 9. max-min
   GramArgs ga{};
@@ -5220,14 +5497,14 @@ size_t carve_workspace(RetrievePlan& p, void* ws) {
   p.qB = static_cast<uint32_t*>(take((size_t)p.S * p.L * p.Hk * 2 * (p.D / 32) * 64 * 16));
   p.tau = static_cast<uint32_t*>(take(lists * 4));
   p.cnt = static_cast<uint32_t*>(take(lists * 4));
-  p.samp = static_cast<float*>(take((size_t)p.S * p.NLs * (size_t)p.m_max * 4));
+  p.samp = static_cast<float*>(take((size_t)p.S * p.NLs * (size_t)p.m_max * 4));   // all_rows: every row's score
   p.below = p.score_mode == 1 ? static_cast<uint64_t*>(take((size_t)p.S * p.NLs * 8)) : nullptr;
   p.lhat = p.hm_prob ? static_cast<float*>(take((size_t)p.S * p.NLs * 4)) : nullptr;
   p.cand_sc = p.hm_prob ? static_cast<float*>(take(lists * (size_t)p.cap * p.Hq * 4)) : nullptr;
   p.left_max = p.hm_prob ? static_cast<uint32_t*>(take(lists * 4)) : nullptr;
   p.alpha = p.hm_prob ? static_cast<float*>(take(lists * (size_t)p.m_max * 4)) : nullptr;
   p.cand_lse = p.hm_prob ? static_cast<float*>(take(lists * (size_t)p.Hq * 4)) : nullptr;
-  p.cand = static_cast<uint64_t*>(take(lists * (size_t)p.cap * 8));
+  p.cand = p.all_rows ? nullptr : static_cast<uint64_t*>(take(lists * (size_t)p.cap * 8));
   p.qcol = static_cast<float*>(take((size_t)p.S * p.L * p.Hk * 16 * 4));
   p.sexp = static_cast<int32_t*>(take((size_t)p.S * 4));
   p.dyn_ctr = static_cast<uint32_t*>(take((size_t)kDynCtr * kDynStride * 4));
