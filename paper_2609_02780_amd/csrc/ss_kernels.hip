@@ -37,7 +37,8 @@
 //   k_gram      fp32 Gram matrix of the pool descriptors.  k_pool_gram does
 //               both in one launch (every Gram block ranks the pool itself)
 //               when a stream's records fit in LDS.
-//   k_maxmin    greedy max-min diversity over the Gram matrix.
+//   k_maxmin    greedy max-min diversity over the Gram matrix.  k_pool_tail does
+//               pool, matrix and max-min of a small pool in one block.
 //
 // Append: k_append (raw rows, pooled keys and the Eq. memory_key descriptor in
 // one pass), or k_kmeans (per-frame k-means compression and the pooled keys) and
@@ -3532,34 +3533,48 @@ struct GramArgs {
   float* gram;          // [S][pool][ld]
 };
 
-// Tile (ti, tj) of stream s from the pool's frame ids `ids` (pn of them);
-// called by the whole block, waves 0..3 compute, `part` is 4 KiB of LDS.
+// Quarter q of the dimensions of tile (ti, tj) of stream s's Gram matrix, from
+// the pool's frame ids `ids` (pn of them): lane l holds tile rows 4 (l >> 4) + j,
+// column l & 15.
 template <int NST>   // 16-dimension steps per wave: dim / 64
+__device__ __forceinline__ f32x4 gram_quarter(const GramArgs& a, int s, int ti, int tj, int pn, const int32_t* ids,
+                                              int w) {
+  const int lane = threadIdx.x & (kWave - 1);
+  constexpr int dim = 64 * NST;
+  // rows past the pool repeat its last row: they only feed tile entries that
+  // are never stored
+  const int ri = min(ti * 16 + (lane & 15), pn - 1), rj = min(tj * 16 + (lane & 15), pn - 1);
+  const float* xi = a.desc[s] + (size_t)ids[ri] * dim + w * (dim / 4) + 4 * (lane >> 4);
+  const float* xj = a.desc[s] + (size_t)ids[rj] * dim + w * (dim / 4) + 4 * (lane >> 4);
+  float4 va[NST], vb[NST];
+#pragma unroll
+  for (int u = 0; u < NST; ++u) va[u] = *reinterpret_cast<const float4*>(xi + 16 * u);
+  if (ti != tj) {   // uniform; a diagonal tile has one set of rows
+#pragma unroll
+    for (int u = 0; u < NST; ++u) vb[u] = *reinterpret_cast<const float4*>(xj + 16 * u);
+  } else {
+#pragma unroll
+    for (int u = 0; u < NST; ++u) vb[u] = va[u];
+  }
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < NST; ++u) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].x, vb[u].x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].y, vb[u].y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].z, vb[u].z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].w, vb[u].w, acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// Tile (ti, tj); called by the whole block, waves 0..3 compute, `part` is 4 KiB
+// of LDS.
+template <int NST>
 __device__ __forceinline__ void gram_tile(const GramArgs& a, int s, int ti, int tj, int pn,
                                           const int32_t* ids, float (*part)[256]) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
-  constexpr int dim = 64 * NST;
   if (w < 4) {
-    // rows past the pool repeat its last row: they only feed tile entries that
-    // are never stored
-    const int ri = min(ti * 16 + (lane & 15), pn - 1), rj = min(tj * 16 + (lane & 15), pn - 1);
-    const float* xi = a.desc[s] + (size_t)ids[ri] * dim + w * (dim / 4) + 4 * (lane >> 4);
-    const float* xj = a.desc[s] + (size_t)ids[rj] * dim + w * (dim / 4) + 4 * (lane >> 4);
-    float4 va[NST], vb[NST];
-#pragma unroll
-    for (int u = 0; u < NST; ++u) {
-      va[u] = *reinterpret_cast<const float4*>(xi + 16 * u);
-      vb[u] = *reinterpret_cast<const float4*>(xj + 16 * u);
-    }
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int u = 0; u < NST; ++u) {
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].x, vb[u].x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].y, vb[u].y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].z, vb[u].z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].w, vb[u].w, acc, 0, 0, 0);
-    }
-    // lane l holds tile rows 4 (l >> 4) + j, column l & 15
+    const f32x4 acc = gram_quarter<NST>(a, s, ti, tj, pn, ids, w);
 #pragma unroll
     for (int j = 0; j < 4; ++j) part[w][(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
   }
@@ -3607,12 +3622,67 @@ __global__ __launch_bounds__(1024) void k_pool_gram(VoteArgs va, GramArgs a) {
   gram_tile<NST>(a, s, ti, tj, pn, ids, part);
 }
 
-// k_gram<1..N> (pool from the pool kernel: va null) and k_pool_gram<1..N>
-// launchers indexed by dim / 64 - 1
-using GramLaunch = void (*)(dim3, const VoteArgs*, const GramArgs&, hipStream_t);
+// Pool, Gram matrix and max-min of a stream in one block, for pools of at most
+// kTailPool frames: few enough tiles that the block's four groups of four waves
+// form them about as fast as as many blocks, and the picks read the distances
+// from LDS, so that max-min's launch and its read of the matrix go away.  The
+// same sums in the same order as k_pool_gram's.
+constexpr int kTailPool = 32;
 template <int NST>
-void launch_gram_n(dim3 g, const VoteArgs* va, const GramArgs& a, hipStream_t st) {
-  if (va) hipLaunchKernelGGL(k_pool_gram<NST>, g, dim3(1024), 0, st, *va, a);
+__global__ __launch_bounds__(1024) void k_pool_tail(VoteArgs va, GramArgs a, MaxminArgs ma) {
+  __shared__ PoolShared psh;
+  __shared__ int32_t ids[kMaxPool];
+  __shared__ float part[4][4][256];
+  __shared__ uint32_t d_lds[kTailPool * kGramLdsPool];
+  __shared__ int32_t pvotes[kTailPool];
+  __shared__ float pmass[kTailPool];
+  __shared__ int sel[kMaxSelect];
+  const int s = blockIdx.x;
+  const int pn = pool_select(va, s, psh, ids, true);
+  __syncthreads();
+  if ((int)threadIdx.x < pn) {   // the ordered pool's records are left in shi / slo
+    const uint64_t h = psh.shi[threadIdx.x], l = psh.slo[threadIdx.x];
+    const uint64_t mb = (h << 32) | (l >> 32);
+    pvotes[threadIdx.x] = (int32_t)(h >> 32);
+    pmass[threadIdx.x] = (float)((double)(int64_t)(mb ^ 0x8000000000000000ull) * ldexp(1.0, -va.sexp[s]));
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = w >> 2;
+  const int nt = (pn + 15) / 16, np = nt * (nt + 1) / 2;
+  for (int p0 = 0; p0 < np; p0 += 4) {
+    int ti = 0, left = p0 + grp;   // tile p of the upper triangle, row by row
+    while (ti < nt && left >= nt - ti) { left -= nt - ti; ++ti; }
+    const int tj = ti + left;
+    if (ti < nt) {   // the same for a group of waves
+      const f32x4 acc = gram_quarter<NST>(a, s, ti, tj, pn, ids, w & 3);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) part[grp][w & 3][(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
+    }
+    __syncthreads();
+    if (ti < nt) {
+      const int e = threadIdx.x & 255, pi = ti * 16 + (e >> 4), pj = tj * 16 + (e & 15);
+      const float v = ((part[grp][0][e] + part[grp][1][e]) + part[grp][2][e]) + part[grp][3][e];
+      if (pi < pn && pj < pn) {
+        const uint32_t d = pi != pj ? ord_u32(1.0f - v) : 0u;
+        d_lds[pi * kGramLdsPool + pj] = d;
+        d_lds[pj * kGramLdsPool + pi] = d;
+      }
+    }
+    __syncthreads();
+  }
+  const int K = min(ma.n_select, pn);
+  maxmin_greedy_lds(d_lds, pn, K, sel);
+  __syncthreads();
+  maxmin_write(ma, s, K, sel, ids, pvotes, pmass);
+}
+
+// k_gram<1..N> (pool from the pool kernel: va null), k_pool_gram<1..N> and
+// k_pool_tail<1..N> (with max-min: ma) launchers indexed by dim / 64 - 1
+using GramLaunch = void (*)(dim3, const VoteArgs*, const GramArgs&, const MaxminArgs*, hipStream_t);
+template <int NST>
+void launch_gram_n(dim3 g, const VoteArgs* va, const GramArgs& a, const MaxminArgs* ma, hipStream_t st) {
+  if (ma) hipLaunchKernelGGL(k_pool_tail<NST>, g, dim3(1024), 0, st, *va, a, *ma);
+  else if (va) hipLaunchKernelGGL(k_pool_gram<NST>, g, dim3(1024), 0, st, *va, a);
   else hipLaunchKernelGGL(k_gram<NST>, g, dim3(256), 0, st, a);
 }
 template <int... I>
@@ -5300,9 +5370,15 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
   // pool and Gram matrix in one launch when every record fits in LDS
   const bool pool_gram = p.f_max <= kPoolSort;
   if (!pool_gram) hipLaunchKernelGGL(k_votes_pool, dim3(p.S), dim3(1024), 0, st, va);
-  gram_launchers<kMaxDescDim / 64>()[ga.dim / 64 - 1](dim3(p.S * ga.tiles * ga.tiles), pool_gram ? &va : nullptr,
-                                                      ga, st);
-  hipLaunchKernelGGL(k_maxmin, dim3(p.S), dim3(1024), 0, st, ma);
+  // and max-min too in one block a stream for small pools.  Per call, two launches
+  // / one: a pool of 16 at any width 29.4 / 26.0 us (128 elements), 37.3 / 34.7
+  // (1,024); of 32 at 256 elements 32.7 / 30.8, at 512 176.7 / 174.5 (the pool
+  // half full) and 33.3 / 32.7 (full), but at 1,024 39.3 / 41.9, and of 64 at 512
+  // 47.6 / 61.9: one CU's matrix cores and L2 reads take longer than the boundary.
+  const bool tail = pool_gram && (p.pool <= 16 || (p.pool <= kTailPool && ga.dim <= 512));
+  gram_launchers<kMaxDescDim / 64>()[ga.dim / 64 - 1](dim3(tail ? p.S : p.S * ga.tiles * ga.tiles),
+                                                      pool_gram ? &va : nullptr, ga, tail ? &ma : nullptr, st);
+  if (!tail) hipLaunchKernelGGL(k_maxmin, dim3(p.S), dim3(1024), 0, st, ma);
   return hipGetLastError();
 }
 
