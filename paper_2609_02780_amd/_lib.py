@@ -131,7 +131,4 @@ def check(status: int) -> None:
 
 
 def ptr_array(ptrs) -> C.Array:
-    arr = (_P * max(1, len(ptrs)))()
-    for i, p in enumerate(ptrs):
-        arr[i] = p
-    return arr
+    return (_P * max(1, len(ptrs)))(*ptrs)

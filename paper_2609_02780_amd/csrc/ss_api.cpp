@@ -173,6 +173,7 @@ double poisson_tail(double lam, int r) {
   for (int i = r; i < r + 2000 && term > 1e-300; ++i) {
     sum += term;
     term *= lam / (i + 1);
+    if (i > lam && term < 1e-20 * sum) break;   // falling terms that no longer change the sum
   }
   return sum;
 }
@@ -193,8 +194,14 @@ double poisson_cdf(double lam, int r) {
 // P(Poisson(3 r) <= r - 1), are both at most kFallbackOdds per list.
 constexpr double kFallbackOdds = 2e-7;
 int64_t sample_rank(int64_t kk, int64_t E) {
+  // the second condition does not depend on the list: the first rank that meets it
+  static const int first = [] {
+    int r = 1;
+    while (r < kSampleRank && poisson_cdf(3.0 * (double)r, r - 1) > kFallbackOdds) ++r;
+    return r;
+  }();
   const int64_t rmax = std::min<int64_t>(kk, kSampleRank);
-  for (int64_t r = 1; r < rmax; ++r)
+  for (int64_t r = first; r < rmax; ++r)
     if (poisson_tail((double)r * (double)kk / (double)E, (int)r) <= kFallbackOdds &&
         poisson_cdf(3.0 * (double)r, (int)r - 1) <= kFallbackOdds)
       return r;
@@ -386,9 +393,15 @@ ss_status retrieve_common(ss_index* const* idx, int32_t n_streams, const void* c
   if (!frame_ids || !votes || !mass || !n_out)
     return fail(SS_ERR_INVALID_ARGUMENT, "an output pointer is NULL");
   if (!ws || !aligned(ws, 256)) return fail(SS_ERR_WORKSPACE, "workspace NULL or not 256-byte aligned");
-  const size_t need = batch_ws(idx, n_streams, n_q, prm, true);
-  if (ws_bytes < need)
+  // a batch of one group (the usual one) is sized by the plan it runs; of more,
+  // every group before the first is enqueued
+  auto too_small = [&](size_t need) {
     return fail(SS_ERR_WORKSPACE, "workspace %zu bytes, %zu needed", ws_bytes, need);
+  };
+  if (n_streams > ss::kMaxStreams) {
+    const size_t need = batch_ws(idx, n_streams, n_q, prm, true);
+    if (ws_bytes < need) return too_small(need);
+  }
   if (dbg && dbg->topk_score == nullptr && dbg->topk_pos != nullptr)
     return fail(SS_ERR_INVALID_ARGUMENT, "debug topk_pos needs topk_score");
   if (dbg && (dbg->vote_hist == nullptr) != (dbg->mass_hist == nullptr))
@@ -398,9 +411,15 @@ ss_status retrieve_common(ss_index* const* idx, int32_t n_streams, const void* c
     const int S = std::min(ss::kMaxStreams, n_streams - s0);
     ss::RetrievePlan p;
     build_plan(p, idx, s0, S, queries, n_q, prm, true);
-    // a workspace too small for the short lists' route may still do for the other
-    if (p.all_rows && ss::carve_workspace(p, nullptr) > ws_bytes) build_plan(p, idx, s0, S, queries, n_q, prm, false);
-    ss::carve_workspace(p, ws);
+    size_t need = ss::carve_workspace(p, ws);
+    if (p.all_rows && need > ws_bytes) {
+      // a workspace too small for the short lists' route may still do for the other
+      const size_t all = need;
+      build_plan(p, idx, s0, S, queries, n_q, prm, false);
+      need = ss::carve_workspace(p, ws);
+      if (need > ws_bytes) return too_small(std::min(all, need));
+    }
+    if (need > ws_bytes) return too_small(need);
     p.out_ids = frame_ids + (size_t)s0 * prm->n_select;
     p.out_votes = votes + (size_t)s0 * prm->n_select;
     p.out_mass = mass + (size_t)s0 * prm->n_select;
@@ -929,7 +948,9 @@ ss_status ss_index_append(ss_index* idx, const void* const* layer_keys, int32_t 
     // the host offsets are reserved before anything is enqueued, so that the
     // bookkeeping after the launch cannot fail and leave the index behind the
     // device state
-    idx->off.reserve(idx->off.size() + (size_t)n_frames);
+    // (grown by doubling: reserving each call's few frames alone would copy them all each time)
+    const size_t want = idx->off.size() + (size_t)n_frames;
+    if (want > idx->off.capacity()) idx->off.reserve(std::max(want, 2 * idx->off.capacity()));
     ss::AppendArgs a{};
     a.L = d.n_layers;
     a.Hk = d.n_kv_heads;

@@ -14,9 +14,16 @@ from . import _lib as L
 _BF16_OK = (torch.bfloat16, torch.int16, torch.uint16)
 
 
+# the current stream's handle without building a torch.cuda.Stream (3 us of a call's host time)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _used_on(stream, *tensors) -> None:
@@ -39,16 +46,34 @@ def sample_plan(n_rows: int, top_k: int) -> tuple[int, int, int, int]:
     return tuple(out)
 
 
-def _check_bf16(t: torch.Tensor, shape, what: str) -> int:
+def _check_bf16(t: torch.Tensor, shape: tuple, what: str, *at) -> int:
+    """The device address of a bfloat16 tensor of this shape (``what % at`` names it)."""
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise ValueError(f"{what} must be a device tensor")
+        raise ValueError(f"{what % at} must be a device tensor")
     if t.dtype not in _BF16_OK:
-        raise ValueError(f"{what} must hold bfloat16 values (got {t.dtype})")
-    if tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{what} has shape {tuple(t.shape)}, expected {tuple(shape)}")
+        raise ValueError(f"{what % at} must hold bfloat16 values (got {t.dtype})")
+    if t.shape != shape:
+        raise ValueError(f"{what % at} has shape {tuple(t.shape)}, expected {shape}")
     if not t.is_contiguous():
-        raise ValueError(f"{what} must be contiguous")
+        raise ValueError(f"{what % at} must be contiguous")
     return t.data_ptr()
+
+
+def _query_pointers(indices, queries):
+    """Device addresses of ``queries[s][l]`` (stream-major) and each stream's token count, as ctypes arrays."""
+    S = len(indices)
+    if len(queries) != S:
+        raise ValueError(f"expected queries for {S} streams, got {len(queries)}")
+    ptrs, n_q = [], []
+    for s, (x, qs) in enumerate(zip(indices, queries)):
+        if len(qs) != x.n_layers:
+            raise ValueError(f"stream {s}: expected {x.n_layers} query tensors")
+        nq = qs[0].shape[1]
+        n_q.append(nq)
+        shape = (x.n_q_heads, nq, x.head_dim)
+        for l, q in enumerate(qs):
+            ptrs.append(_check_bf16(q, shape, "queries[%d][%d]", s, l))
+    return L.ptr_array(ptrs), (C.c_int32 * S)(*n_q)
 
 
 class ShallowIndex:
@@ -120,7 +145,7 @@ class ShallowIndex:
         """Append frames; ``layer_keys[l]`` is ``[H_kv][n_frames*n_tokens][d]`` bfloat16.
         ``compress`` is ``None`` or ``(n_centroids, n_iters)``.  Returns the first frame id."""
         shape = (self.n_kv_heads, n_frames * n_tokens, self.head_dim)
-        ptrs = [_check_bf16(t, shape, f"layer_keys[{l}]") for l, t in enumerate(layer_keys)]
+        ptrs = [_check_bf16(t, shape, "layer_keys[%d]", l) for l, t in enumerate(layer_keys)]
         if len(ptrs) != self.n_layers:
             raise ValueError(f"expected {self.n_layers} key tensors, got {len(ptrs)}")
         comp = L.Compress(*compress) if compress is not None else None
@@ -151,7 +176,7 @@ class ShallowIndex:
         """fp32 scores of one list over rows ``[row0, row0 + n_rows)`` (parity checks)."""
         n_q = queries[0].shape[1]
         qshape = (self.n_q_heads, n_q, self.head_dim)
-        qp = [_check_bf16(q, qshape, f"queries[{l}]") for l, q in enumerate(queries)]
+        qp = [_check_bf16(q, qshape, "queries[%d]", l) for l, q in enumerate(queries)]
         if n_rows is None:
             n_rows = self.n_rows - row0
         out = torch.empty(max(n_rows, 1), dtype=torch.float32, device=self.arena.device)
@@ -185,28 +210,18 @@ class Retriever:
         self._handles = L.ptr_array([x.handle.value for x in self.indices])
 
     def workspace_bytes(self, n_q) -> int:
-        nq = (C.c_int32 * len(self.indices))(*n_q)
+        nq = n_q if isinstance(n_q, C.Array) else (C.c_int32 * len(self.indices))(*n_q)
         need = L.lib().ss_retrieve_workspace_bytes(self._handles, len(self.indices), nq, C.byref(self.params))
         if need == 0:
             raise L.SSError(L.SS_ERR_INVALID_ARGUMENT, L.lib().ss_last_error().decode())
         return need
 
     def _marshal(self, queries):
-        S = len(self.indices)
-        if len(queries) != S:
-            raise ValueError(f"expected queries for {S} streams, got {len(queries)}")
-        ptrs, n_q = [], []
-        for s, (x, qs) in enumerate(zip(self.indices, queries)):
-            if len(qs) != x.n_layers:
-                raise ValueError(f"stream {s}: expected {x.n_layers} query tensors")
-            nq = qs[0].shape[1]
-            n_q.append(nq)
-            for l, q in enumerate(qs):
-                ptrs.append(_check_bf16(q, (x.n_q_heads, nq, x.head_dim), f"queries[{s}][{l}]"))
-        need = self.workspace_bytes(n_q)
+        qp, nq = _query_pointers(self.indices, queries)
+        need = self.workspace_bytes(nq)
         if self._ws is None or self._ws.numel() < need:
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.frame_ids.device)
-        return L.ptr_array(ptrs), (C.c_int32 * S)(*n_q)
+        return qp, nq
 
     def __call__(self, queries, stream=None):
         """``queries[s][l]``: ``[H_q][n_q][d]`` bfloat16.  Returns device tensors
@@ -224,17 +239,8 @@ class Retriever:
         device workspace instead of this object's (no device allocation by the
         library or here).  Returns the same reused output buffers."""
         S = len(self.indices)
-        if len(queries) != S:
-            raise ValueError(f"expected queries for {S} streams, got {len(queries)}")
-        ptrs, n_q = [], []
-        for s, (x, qs) in enumerate(zip(self.indices, queries)):
-            if len(qs) != x.n_layers:
-                raise ValueError(f"stream {s}: expected {x.n_layers} query tensors")
-            nq = qs[0].shape[1]
-            n_q.append(nq)
-            for l, q in enumerate(qs):
-                ptrs.append(_check_bf16(q, (x.n_q_heads, nq, x.head_dim), f"queries[{s}][{l}]"))
-        L.check(L.lib().ss_retrieve_noalloc(self._handles, S, L.ptr_array(ptrs), (C.c_int32 * S)(*n_q),
+        qp, nq = _query_pointers(self.indices, queries)
+        L.check(L.lib().ss_retrieve_noalloc(self._handles, S, qp, nq,
                                             C.byref(self.params), _stream_handle(stream),
                                             self.frame_ids.data_ptr(), self.votes.data_ptr(),
                                             self.mass.data_ptr(), self.n_out.data_ptr()))
@@ -291,23 +297,13 @@ class PooledRanker:
         """``queries[s][l]``: ``[H_q][n_q][d]`` bfloat16.  Returns device tensors
         ``(frame_ids, scores, n_out)`` (views of reused buffers)."""
         S = len(self.indices)
-        if len(queries) != S:
-            raise ValueError(f"expected queries for {S} streams, got {len(queries)}")
-        ptrs, n_q = [], []
-        for s, (x, qs) in enumerate(zip(self.indices, queries)):
-            if len(qs) != x.n_layers:
-                raise ValueError(f"stream {s}: expected {x.n_layers} query tensors")
-            nq = qs[0].shape[1]
-            n_q.append(nq)
-            for l, q in enumerate(qs):
-                ptrs.append(_check_bf16(q, (x.n_q_heads, nq, x.head_dim), f"queries[{s}][{l}]"))
-        nqa = (C.c_int32 * S)(*n_q)
+        qp, nqa = _query_pointers(self.indices, queries)
         need = L.lib().ss_pooled_workspace_bytes(self._handles, S, nqa, self.n_select)
         if need == 0:
             raise L.SSError(L.SS_ERR_INVALID_ARGUMENT, L.lib().ss_last_error().decode())
         if self._ws is None or self._ws.numel() < need:
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.frame_ids.device)
-        L.check(L.lib().ss_retrieve_pooled(self._handles, S, L.ptr_array(ptrs), nqa, self.n_select,
+        L.check(L.lib().ss_retrieve_pooled(self._handles, S, qp, nqa, self.n_select,
                                            self._ws.data_ptr(), self._ws.numel(), _stream_handle(stream),
                                            self.frame_ids.data_ptr(), self.scores.data_ptr(),
                                            self.n_out.data_ptr()))
@@ -363,7 +359,7 @@ class LongClusters:
         if len(queries) != x.n_layers:
             raise ValueError(f"expected {x.n_layers} query tensors")
         nq = queries[0].shape[1]
-        ptrs = [_check_bf16(q, (x.n_q_heads, nq, x.head_dim), f"queries[{l}]") for l, q in enumerate(queries)]
+        ptrs = [_check_bf16(q, (x.n_q_heads, nq, x.head_dim), "queries[%d]", l) for l, q in enumerate(queries)]
         need = L.lib().ss_clusters_retrieve_workspace_bytes(self._h)
         if self._qws is None or self._qws.numel() < need:
             self._qws = torch.empty(need, dtype=torch.uint8, device=self.arena.device)
