@@ -3109,6 +3109,7 @@ struct VoteArgs {
 // returns pn.  One block of 1024 threads per stream.
 constexpr int kVoteBins = 2048;   // vote histogram bins (the last one collects larger counts)
 constexpr int kTieRank = 128;     // frames tied at the cut ranked by counting
+constexpr int kVoteRank = 256;    // voted frames up to which all are ranked by counting
 
 struct PoolShared {
   uint64_t shi[kPoolSort];
@@ -3201,58 +3202,82 @@ __device__ int pool_select(const VoteArgs& a, int s, PoolShared& sh, int* lds_id
       l = __hip_atomic_load(&rl[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
-  uint64_t ch = 0, cl = 0;
-  if (n_voted > P) {
-    bool cut = false;
-    if (in_lds) {
-      // vote histogram; pair of bins (2q, 2q + 1) per thread, q from the top
-      for (int i = threadIdx.x; i < kVoteBins; i += blockDim.x) sh.vh[i] = 0;
-      __syncthreads();
-      for (int i = threadIdx.x; i < n_voted; i += blockDim.x)
-        atomicAdd(&sh.vh[min((uint32_t)(sh.shi[i] >> 32), (uint32_t)(kVoteBins - 1))], 1u);
-      __syncthreads();
-      const int q = kVoteBins / 2 - 1 - (int)threadIdx.x;   // blockDim == kVoteBins / 2
-      const int hb = (int)sh.vh[2 * q + 1], lb = (int)sh.vh[2 * q];
-      int tot;
-      const int above = block_excl_scan(hb + lb, sh.scan, tot);   // records in higher bin pairs
-      if (above < P && P <= above + hb) { sh.vstar = 2 * q + 1; sh.above = above; sh.inb = hb; }
-      else if (above + hb < P && P <= above + hb + lb) { sh.vstar = 2 * q; sh.above = above + hb; sh.inb = lb; }
-      __syncthreads();
-      const int vstar = sh.vstar, need = P - sh.above, inb = sh.inb;
-      if (vstar >= 1 && vstar < kVoteBins - 1 && inb <= kTieRank) {
-        if (inb == need) {
-          ch = (uint64_t)(uint32_t)vstar << 32;   // every frame with >= v* votes
-          cl = 0;
-        } else {
-          for (int i = threadIdx.x; i < n_voted; i += blockDim.x)
-            if ((int)(sh.shi[i] >> 32) == vstar) sh.tl[atomicAdd(&sh.ntie, 1u)] = i;
-          __syncthreads();
-          if ((int)threadIdx.x < inb) {
-            const int me = sh.tl[threadIdx.x];
-            const uint64_t h = sh.shi[me], l = sh.slo[me];
-            int rank = 0;
-            for (int k = 0; k < inb; ++k) {
-              const int o = sh.tl[k];
-              rank += rec_less(h, l, sh.shi[o], sh.slo[o]);
+  // few voted frames: every record's rank by counting, in one pass (1024 / 2^lg
+  // threads a record), instead of histogram, cut and gather.  Measured on 600
+  // compressed frames: 47.0 -> 45.1 us a call; with up to 512 frames on this path
+  // the 10-minute index went from 109.9 to 113.5.
+  if (n_voted <= kVoteRank) {
+    const int lg = n_voted <= 64 ? 6 : n_voted <= 128 ? 7 : 8;
+    const int parts = 1024 >> lg, i = (int)threadIdx.x / parts, part = (int)threadIdx.x & (parts - 1);
+    uint64_t h = 0, l = 0;
+    int rank = 0;
+    if (i < n_voted) {
+      h = sh.shi[i];
+      l = sh.slo[i];
+      for (int j = part; j < n_voted; j += parts) rank += rec_less(h, l, sh.shi[j], sh.slo[j]);
+    }
+    for (int o = 1; o < parts; o <<= 1) rank += __shfl_xor(rank, o);
+    __syncthreads();   // every record has been compared with
+    if (i < n_voted && part == 0 && rank < pn) {
+      sh.shi[rank] = h;   // records are distinct: ranks form a permutation
+      sh.slo[rank] = l;
+    }
+  } else {
+    uint64_t ch = 0, cl = 0;
+    if (n_voted > P) {
+      bool cut = false;
+      if (in_lds) {
+        // vote histogram; pair of bins (2q, 2q + 1) per thread, q from the top
+        for (int i = threadIdx.x; i < kVoteBins; i += blockDim.x) sh.vh[i] = 0;
+        __syncthreads();
+        for (int i = threadIdx.x; i < n_voted; i += blockDim.x)
+          atomicAdd(&sh.vh[min((uint32_t)(sh.shi[i] >> 32), (uint32_t)(kVoteBins - 1))], 1u);
+        __syncthreads();
+        const int q = kVoteBins / 2 - 1 - (int)threadIdx.x;   // blockDim == kVoteBins / 2
+        const int hb = (int)sh.vh[2 * q + 1], lb = (int)sh.vh[2 * q];
+        int tot;
+        const int above = block_excl_scan(hb + lb, sh.scan, tot);   // records in higher bin pairs
+        if (above < P && P <= above + hb) { sh.vstar = 2 * q + 1; sh.above = above; sh.inb = hb; }
+        else if (above + hb < P && P <= above + hb + lb) { sh.vstar = 2 * q; sh.above = above + hb; sh.inb = lb; }
+        __syncthreads();
+        const int vstar = sh.vstar, need = P - sh.above, inb = sh.inb;
+        if (vstar >= 1 && vstar < kVoteBins - 1 && inb <= kTieRank) {
+          if (inb == need) {
+            ch = (uint64_t)(uint32_t)vstar << 32;   // every frame with >= v* votes
+            cl = 0;
+          } else {
+            for (int i = threadIdx.x; i < n_voted; i += blockDim.x)
+              if ((int)(sh.shi[i] >> 32) == vstar) sh.tl[atomicAdd(&sh.ntie, 1u)] = i;
+            __syncthreads();
+            if ((int)threadIdx.x < inb) {
+              const int me = sh.tl[threadIdx.x];
+              const uint64_t h = sh.shi[me], l = sh.slo[me];
+              int rank = 0;
+              for (int k = 0; k < inb; ++k) {
+                const int o = sh.tl[k];
+                rank += rec_less(h, l, sh.shi[o], sh.slo[o]);
+              }
+              if (rank == need - 1) { sh.cut_hi = h; sh.cut_lo = l; }   // records are distinct
             }
-            if (rank == need - 1) { sh.cut_hi = h; sh.cut_lo = l; }   // records are distinct
+            __syncthreads();
+            ch = sh.cut_hi;
+            cl = sh.cut_lo;
           }
-          __syncthreads();
-          ch = sh.cut_hi;
-          cl = sh.cut_lo;
+          cut = true;
         }
-        cut = true;
+      }
+      if (!cut) radix_select_u128(get, n_voted, (uint32_t)P, sh.hist, sh.res, ch, cl);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n_voted; i += blockDim.x) {
+      uint64_t h, l;
+      get(i, h, l);
+      if (h > ch || (h == ch && l >= cl)) {
+        const uint32_t slot = atomicAdd(&sh.ngather, 1u);
+        if (slot < (uint32_t)kMaxPool) { sh.ghi[slot] = h; sh.glo[slot] = l; }
       }
     }
-    if (!cut) radix_select_u128(get, n_voted, (uint32_t)P, sh.hist, sh.res, ch, cl);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < n_voted; i += blockDim.x) {
-    uint64_t h, l;
-    get(i, h, l);
-    if (h > ch || (h == ch && l >= cl)) {
-      const uint32_t slot = atomicAdd(&sh.ngather, 1u);
-      if (slot < (uint32_t)kMaxPool) { sh.ghi[slot] = h; sh.glo[slot] = l; }
+    __syncthreads();
     }
   }
   __syncthreads();
@@ -3273,6 +3298,7 @@ __device__ int pool_select(const VoteArgs& a, int s, PoolShared& sh, int* lds_id
       sh.shi[rank] = h;   // records are distinct: ranks form a permutation
       sh.slo[rank] = l;
     }
+  }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < P; i += blockDim.x) {

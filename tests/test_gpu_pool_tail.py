@@ -49,3 +49,20 @@ def test_pools(Hk, d, K, mult, F):
             picked = out["frame_ids"][s, :n]
             np.testing.assert_array_equal(out["votes"][s, :n], out["vote_hist"][s][picked])
             np.testing.assert_array_equal(out["mass"][s, :n], out["mass_hist"][s][picked])
+
+
+@pytest.mark.parametrize("F", [1, 63, 64, 65, 128, 129, 255, 256, 257, 300])
+def test_every_frame_voted(F):
+    """k beyond the rows: every frame holds votes (equal ones), so the pool is
+    the frames of largest mass, at voted counts around those ranked by counting."""
+    import paper_2609_02780_amd as P
+    T, K, mult = 2, 12, 4
+    cfg = W.Config("allvoted", 1, 4, 2, 64, T, 2, 700, K, n_frames=F, n_planted=1, pool_mult=mult)
+    q, keys = W.make_stream(cfg, W.stream_specs(cfg)[0], seed=F)
+    g = P.ShallowIndex(1, 4, 2, 64, F, F * T)
+    g.append([dev_bf16(x) for x in keys], F, T)
+    o = O.Index(1, 4, 2, 64)
+    o.append(keys, F, T)
+    out = P.Retriever([g], 700, K, mult).debug([[dev_bf16(x) for x in q]])
+    assert np.all(out["vote_hist"][0, :F] == 4 * T) and out["pool_n"][0] == min(K * mult, F)
+    staged_check(o, q, out, 0, 700, K, mult)
