@@ -3278,27 +3278,24 @@ __device__ int pool_select(const VoteArgs& a, int s, PoolShared& sh, int* lds_id
       }
     }
     __syncthreads();
+    // rank by counting, 8 threads per record (pn <= kMaxPool = 256 = blockDim / 8 * 2)
+    for (int i0 = 0; i0 < pn; i0 += (int)blockDim.x / 8) {
+      const int i = i0 + (int)threadIdx.x / 8, part = threadIdx.x & 7;
+      int rank = 0;
+      uint64_t h = 0, l = 0;
+      if (i < pn) {
+        h = sh.ghi[i];
+        l = sh.glo[i];
+        for (int j = part; j < pn; j += 8) rank += rec_less(h, l, sh.ghi[j], sh.glo[j]);
+      }
+      rank += __shfl_xor(rank, 1);
+      rank += __shfl_xor(rank, 2);
+      rank += __shfl_xor(rank, 4);
+      if (i < pn && part == 0) {
+        sh.shi[rank] = h;   // records are distinct: ranks form a permutation
+        sh.slo[rank] = l;
+      }
     }
-  }
-  __syncthreads();
-  // rank by counting, 8 threads per record (pn <= kMaxPool = 256 = blockDim / 8 * 2)
-  for (int i0 = 0; i0 < pn; i0 += (int)blockDim.x / 8) {
-    const int i = i0 + (int)threadIdx.x / 8, part = threadIdx.x & 7;
-    int rank = 0;
-    uint64_t h = 0, l = 0;
-    if (i < pn) {
-      h = sh.ghi[i];
-      l = sh.glo[i];
-      for (int j = part; j < pn; j += 8) rank += rec_less(h, l, sh.ghi[j], sh.glo[j]);
-    }
-    rank += __shfl_xor(rank, 1);
-    rank += __shfl_xor(rank, 2);
-    rank += __shfl_xor(rank, 4);
-    if (i < pn && part == 0) {
-      sh.shi[rank] = h;   // records are distinct: ranks form a permutation
-      sh.slo[rank] = l;
-    }
-  }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < P; i += blockDim.x) {
