@@ -1972,10 +1972,9 @@ __device__ __forceinline__ int& list_mass_exponent() {
   return xs;
 }
 
-// The sample (m <= N * 1024 scores, N <= kThrItems, chosen at launch from the
-// largest sample) sits in registers.  The blocks of a stream also clear its
-// frame accumulators.
-template <int N>
+// The sample (m <= N * BT scores, chosen at launch from the largest sample)
+// sits in registers.  The blocks of a stream also clear its frame accumulators.
+template <int N, int BT>
 __device__ __forceinline__ void thresh_list(const ListArgs& a) {
   __shared__ uint32_t hist[kSelHist];
   __shared__ uint32_t res[4];
@@ -1988,7 +1987,7 @@ __device__ __forceinline__ void thresh_list(const ListArgs& a) {
   {
     int32_t* vg = a.votes_g + (size_t)s * a.f_max;
     int64_t* mg = a.massfx_g + (size_t)s * a.f_max;
-    for (int f = ll * 1024 + threadIdx.x; f < a.f[s]; f += a.NL * 1024) {
+    for (int f = ll * BT + threadIdx.x; f < a.f[s]; f += a.NL * BT) {
       vg[f] = 0;
       mg[f] = 0;
     }
@@ -2003,10 +2002,10 @@ __device__ __forceinline__ void thresh_list(const ListArgs& a) {
   uint32_t mn = 0xFFFFFFFFu, mx = 0;
   // every load issued at once, from clamped in-bounds indices (m >= 1)
 #pragma unroll
-  for (int it = 0; it < N; ++it) x[it] = __float_as_uint(v[min((int)threadIdx.x + it * 1024, m - 1)]);
+  for (int it = 0; it < N; ++it) x[it] = __float_as_uint(v[min((int)threadIdx.x + it * BT, m - 1)]);
 #pragma unroll
   for (int it = 0; it < N; ++it) {
-    ok[it] = (int)threadIdx.x + it * 1024 < m;
+    ok[it] = (int)threadIdx.x + it * BT < m;
     x[it] = ok[it] ? ord_u32(__uint_as_float(x[it]) + 0.0f) : 0u;
     if (ok[it]) { mn = min(mn, x[it]); mx = max(mx, x[it]); }
   }
@@ -2016,18 +2015,16 @@ __device__ __forceinline__ void thresh_list(const ListArgs& a) {
   if (threadIdx.x == 0) a.tau[list] = t;
 }
 
-// One block per list.  With up to two lists per CU the kernel takes the
-// registers it wants (90 VGPRs: one block per CU); with more lists (the
-// 16-stream batch: 1,536) the dense variant fits two blocks per CU in 64 VGPRs
-// with a few spills, three rounds of blocks instead of six (41 -> 32 us on that
-// batch).
-template <int N>
-__global__ __launch_bounds__(1024) void k_thresh(ListArgs a) {
-  thresh_list<N>(a);
+// One block of BT threads per list, in the registers it wants.
+template <int N, int BT>
+__global__ __launch_bounds__(BT) void k_thresh(ListArgs a) {
+  thresh_list<N, BT>(a);
 }
+// Samples of more than 8,192 scores of many lists: 64 VGPRs with a few spills,
+// two blocks of 1,024 threads per CU instead of one.
 template <int N>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_thresh_dense(ListArgs a) {
-  thresh_list<N>(a);
+  thresh_list<N, 1024>(a);
 }
 
 // k_prep_thresh: query prep, sample scores and the cut-off of one list per
@@ -2176,19 +2173,30 @@ __global__ __launch_bounds__(1024) void k_prep_thresh(PrepArgs pa, PtArgs a) {
   if (threadIdx.x == 0) a.tau[list] = t;
 }
 
-// Launches the cut-off kernel with the fewest sample slots per thread that
-// hold the largest sample.
+// Launches the cut-off kernel with the fewest sample slots per thread that hold
+// the largest sample.  The time of a list is a chain of block-wide barriers,
+// which cost the more the more waves take part, so a small sample gets four
+// waves with 8 slots a thread instead of sixteen with four, most of them empty
+// (whole call, 4 streams x 112 lists of 60,000 rows, m = 547: 202.8 -> 200.7
+// us).  With more than two lists per CU (`dense`) four waves also win on larger
+// samples, for more lists then share a CU: 8 x 96 lists of 176,400 rows (m =
+// 1,608) 717 -> 713 us, 16 ragged streams (m up to 6,430) 1,529.3 -> 1,527.8.
+// With fewer lists a larger sample wants the sixteen waves' loads and counting
+// (1,024-second index, 112 lists, attention probabilities: 174.6 us a call,
+// 176.0 with four waves of 16 slots).
 void launch_thresh(const ListArgs& la, int lists, int m_max, bool dense, hipStream_t st) {
-  const dim3 g(lists), b(1024);
-  if (m_max <= 4096) {
-    if (dense) hipLaunchKernelGGL(k_thresh_dense<4>, g, b, 0, st, la);
-    else hipLaunchKernelGGL(k_thresh<4>, g, b, 0, st, la);
+  const dim3 g(lists), b(1024), b4(256);
+  if (m_max <= 2048) {
+    hipLaunchKernelGGL((k_thresh<8, 256>), g, b4, 0, st, la);
+  } else if (m_max <= 4096) {
+    if (dense) hipLaunchKernelGGL((k_thresh<16, 256>), g, b4, 0, st, la);
+    else hipLaunchKernelGGL((k_thresh<4, 1024>), g, b, 0, st, la);
   } else if (m_max <= 8192) {
-    if (dense) hipLaunchKernelGGL(k_thresh_dense<8>, g, b, 0, st, la);
-    else hipLaunchKernelGGL(k_thresh<8>, g, b, 0, st, la);
+    if (dense) hipLaunchKernelGGL((k_thresh<32, 256>), g, b4, 0, st, la);
+    else hipLaunchKernelGGL((k_thresh<8, 1024>), g, b, 0, st, la);
   } else {
     if (dense) hipLaunchKernelGGL(k_thresh_dense<kThrItems>, g, b, 0, st, la);
-    else hipLaunchKernelGGL(k_thresh<kThrItems>, g, b, 0, st, la);
+    else hipLaunchKernelGGL((k_thresh<kThrItems, 1024>), g, b, 0, st, la);
   }
 }
 
