@@ -152,10 +152,9 @@ ss_status ss_index_window(const ss_index* idx, int64_t* first_stored, int64_t* f
  * optional_context_compression): the frames that left the detailed window
  * leave the arena too.  Their rows, member counts, descriptors, pooled keys and
  * row offsets are dropped; the stored rows of the detailed frames move to the
- * start of every (layer, KV head) run of the arena (in passes of at most the
- * dropped rows, each a copy kernel on `stream`), so that later appends reuse
- * the space: max_frames and max_rows then bound the frames and rows kept in
- * detail, not the stream's length.  Frame ids stay as they were.  Retrieval,
+ * start of every (layer, KV head) run of the arena (one kernel on `stream`,
+ * in place), so that later appends reuse the space: max_frames and max_rows
+ * then bound the frames and rows kept in detail, not the stream's length.  Frame ids stay as they were.  Retrieval,
  * pooled ranking, absorption and evidence are unchanged by it.  No-op when no
  * frame has left the detailed window since the last compaction.  Its cost is a
  * copy of the kept rows, so compact after absorbing many frames at once.
