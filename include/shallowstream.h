@@ -197,8 +197,8 @@ ss_status ss_index_append(ss_index* idx, const void* const* layer_keys, int32_t 
 /* Workspace bytes ss_retrieve needs for this batch in the indices' current state
  * (0 if the arguments are invalid).  n_q: host array of n_streams token counts.
  * Short lists (head_mode 0, at most 32,768 candidate rows) are sized for the
- * score of every row; ss_retrieve takes a workspace without room for those all
- * the same, on the route of longer lists. */
+ * score of every row too; ss_retrieve takes a workspace without room for those
+ * all the same, on the route of longer lists. */
 size_t ss_retrieve_workspace_bytes(ss_index* const* idx, int32_t n_streams, const int32_t* n_q,
                                    const ss_retrieve_params* params);
 
@@ -260,10 +260,13 @@ ss_status ss_retrieve_noalloc(ss_index* const* idx, int32_t n_streams, const voi
  *   pool        int32 [n_streams][pool_mult*n_select] the vote-ranked pool, -1 padded;
  *   pool_n      int32 [n_streams];
  *   list_stats  int32 [n_streams][n_lists][2]: candidates kept by the streaming
- *               pass, and 1 if the list took the exact fallback path.  Lists
- *               short enough to be selected from every row's score have neither:
- *               the rows at or above the k-th score, and 1 if those exceed the
- *               candidate capacity. */
+ *               pass, and nonzero if the list took the exact fallback path.
+ *               Short lists that ss_retrieve would select from every row's score
+ *               take the route of the streaming pass when these are asked for
+ *               (logits, lists and votes are the same bit for bit on either;
+ *               with attention probabilities the normaliser's rounding differs,
+ *               about 1e-6 relative); with a NULL here the call takes
+ *               ss_retrieve's route. */
 typedef struct {
   int32_t* topk_pos;
   float* topk_score;

@@ -264,10 +264,10 @@ ss_status check_params(const ss_retrieve_params* p, int Hk, int D) {
 }
 
 // Builds the plan of streams [s0, s0 + S) of a validated batch (`queries` may be
-// NULL when only the workspace size is wanted).  all_rows: take the route of
-// short lists where the batch has none longer than kAllRows.
+// NULL when only the workspace size is wanted), on the route of short lists where
+// that is the better one.
 void build_plan(ss::RetrievePlan& p, ss_index* const* idx, int s0, int S, const void* const* queries,
-                const int32_t* n_q, const ss_retrieve_params* prm, bool all_rows) {
+                const int32_t* n_q, const ss_retrieve_params* prm) {
   std::memset(&p, 0, sizeof p);
   const ss_index_desc& d = idx[0]->desc;
   p.S = S;
@@ -324,7 +324,7 @@ void build_plan(ss::RetrievePlan& p, ss_index* const* idx, int s0, int S, const 
     hist = (int)std::max<int64_t>(hist, x->desc.max_frames);
   }
   p.f_max = std::max(p.f_max, 1);
-  p.m_max = std::max(p.m_max, 1);
+  p.m_samp = p.m_max = std::max(p.m_max, 1);
   // Short lists: score and keep every row instead of sampling, streaming the
   // candidates and reading the keys twice.  What it costs is writing and reading
   // the scores, so beyond 8,192 rows a batch takes it up to 3 M of them.
@@ -333,10 +333,10 @@ void build_plan(ss::RetrievePlan& p, ss_index* const* idx, int s0, int S, const 
   // heads) of 16,384 rows 66.7 / 64.0, of 25,600 (4.1 M) 81.2 / 84.0; 448 lists of
   // 8,192 rows 84 / 65, of 19,200 107 / 110.
   const int64_t lists = (int64_t)p.S * p.NL;
-  if (all_rows && prm->head_mode == 0 && prm->top_k <= ss::kAllTopK && n_max <= ss::kAllRows && p.S * p.L <= 128 &&
+  if (prm->head_mode == 0 && prm->top_k <= ss::kAllTopK && n_max <= ss::kAllRows && p.S * p.L <= 128 &&
       lists <= 512 && (n_max <= 8192 || lists * n_max <= 3'000'000)) {
     p.all_rows = true;
-    p.m_max = (int)((std::max<int64_t>(n_max, 1) + 15) / 16 * 16);   // whole tiles
+    p.m_max = p.m_all = (int)((std::max<int64_t>(n_max, 1) + 15) / 16 * 16);   // whole tiles
   }
   p.cap = (int)candidate_cap(prm->top_k, n_max);
   p.dbg_hist_stride = hist;
@@ -357,23 +357,33 @@ ss_status check_batch(ss_index* const* idx, int32_t n_streams, const int32_t* n_
   return check_params(prm, idx[0]->desc.n_kv_heads, idx[0]->desc.head_dim);
 }
 
-size_t group_ws(ss_index* const* idx, int s0, int S, const int32_t* n_q,
-                const ss_retrieve_params* prm, bool all_rows) {
-  ss::RetrievePlan p;
-  build_plan(p, idx, s0, S, nullptr, n_q, prm, all_rows);
-  return ss::carve_workspace(p, nullptr);
+// The plan's two routes: of longer lists (sample, cut-off, streaming pass), and of
+// short ones where build_plan chose that.
+void take_sampled_route(ss::RetrievePlan& p) {
+  p.all_rows = false;
+  p.m_max = p.m_samp;
+}
+void take_all_rows_route(ss::RetrievePlan& p) {
+  p.all_rows = true;
+  p.m_max = p.m_all;
 }
 
-// The workspace a batch should have (every group on its preferred route), or the
-// one it can do with (`least`: the smaller of each group's two routes).
+// Workspace bytes of a batch.  Every group needs the sampled route's (`least`);
+// the size a caller should have adds room for the route of short lists, where
+// that stays within kNoAllocBytes.
 size_t batch_ws(ss_index* const* idx, int32_t n_streams, const int32_t* n_q,
                 const ss_retrieve_params* prm, bool least) {
   size_t need = 0;
   for (int s0 = 0; s0 < n_streams; s0 += ss::kMaxStreams) {
     const int S = std::min(ss::kMaxStreams, n_streams - s0);
-    size_t g = group_ws(idx, s0, S, n_q, prm, true);
-    if (least || g > ss::kNoAllocBytes) g = std::min(g, group_ws(idx, s0, S, n_q, prm, false));
-    need = std::max(need, g);
+    ss::RetrievePlan p;
+    build_plan(p, idx, s0, S, nullptr, n_q, prm);
+    if (p.all_rows && !least) {
+      const size_t all = ss::carve_workspace(p, nullptr);
+      if (all <= ss::kNoAllocBytes) need = std::max(need, all);
+    }
+    take_sampled_route(p);
+    need = std::max(need, ss::carve_workspace(p, nullptr));
   }
   return need;
 }
@@ -410,16 +420,17 @@ ss_status retrieve_common(ss_index* const* idx, int32_t n_streams, const void* c
   for (int s0 = 0; s0 < n_streams; s0 += ss::kMaxStreams) {
     const int S = std::min(ss::kMaxStreams, n_streams - s0);
     ss::RetrievePlan p;
-    build_plan(p, idx, s0, S, queries, n_q, prm, true);
-    size_t need = ss::carve_workspace(p, ws);
-    if (p.all_rows && need > ws_bytes) {
-      // a workspace too small for the short lists' route may still do for the other
-      const size_t all = need;
-      build_plan(p, idx, s0, S, queries, n_q, prm, false);
-      need = ss::carve_workspace(p, ws);
-      if (need > ws_bytes) return too_small(std::min(all, need));
-    }
+    build_plan(p, idx, s0, S, queries, n_q, prm);
+    // the route of short lists, where the workspace has room for its scores too and
+    // the streaming pass's statistics are not asked for
+    const bool all = p.all_rows && !(dbg && dbg->list_stats) && ss::carve_workspace(p, nullptr) <= ws_bytes;
+    take_sampled_route(p);
+    const size_t need = ss::carve_workspace(p, ws);
     if (need > ws_bytes) return too_small(need);
+    if (all) {
+      take_all_rows_route(p);
+      ss::carve_workspace(p, ws);
+    }
     p.out_ids = frame_ids + (size_t)s0 * prm->n_select;
     p.out_votes = votes + (size_t)s0 * prm->n_select;
     p.out_mass = mass + (size_t)s0 * prm->n_select;

@@ -91,6 +91,7 @@ struct RetrievePlan {
   int k_max;             // max over streams of kk
   bool all_rows;         // short lists (head_mode 0): every row's score is kept and selected from
   int m_max, f_max;
+  int m_samp, m_all;     // m_max of the sampled route and of the short lists'
   int chunk_rows, samp_chunk;
   StreamPlan st[kMaxStreams];
 

@@ -2953,9 +2953,8 @@ __device__ void select_list(const ListArgs& a, int list, SelectShared& sh, uint3
 // largest of the threads' own maxima (k <= 1,024) is a bound that at least k rows
 // reach, one histogram round gives it to within a bin, and the few rows at or above it are selected from as the candidates of
 // longer lists are (or, where too many tie for that, all rows by radix).
-// Nothing can be missed, so there is no fallback; the debug counts are the rows
-// at or above the k-th value, and 1 where those exceed the candidate capacity of
-// longer lists.
+// Nothing can be missed, so there is no fallback, and a call for the candidates'
+// statistics takes the streaming pass instead.
 // Measured at 19,200 rows: 9.5 us (loads 2.7, bound and compaction 2.9, selection
 // 2.4), against about 17 us with radix rounds over all 32 slots a thread.
 constexpr int kAllKeep = 4096;   // rows kept by the bound (they take the place of the frame sums)
@@ -3062,21 +3061,6 @@ __global__ __launch_bounds__(1024) void k_select_all(ListArgs a) {
     }
   }
   __syncthreads();
-  if (a.dbg_stats) {
-    uint32_t low = 0xFFFFFFFFu, top = 0;
-    for (int e = threadIdx.x; e < kk; e += 1024) low = min(low, (uint32_t)(sel[e] >> 32));
-    block_minmax_u32(low, top, mm);
-    if (threadIdx.x == 0) nkeep = 0;
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < N; ++it)
-      if (u[it] >= low) atomicAdd(&nkeep, 1u);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      a.dbg_stats[2 * list] = (int32_t)nkeep;
-      a.dbg_stats[2 * list + 1] = nkeep > (uint32_t)a.cap;
-    }
-  }
   if (a.score_mode == 1) to_probabilities(sel, kk, lse);
   finish_list(a, list, sel, kk, sh.lv, sh.lm);
 }

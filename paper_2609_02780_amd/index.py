@@ -246,8 +246,10 @@ class Retriever:
                                             self.mass.data_ptr(), self.n_out.data_ptr()))
         return self.frame_ids, self.votes, self.mass, self.n_out
 
-    def debug(self, queries, stream=None) -> dict:
-        """One retrieval with every intermediate (synchronises; parity checks only)."""
+    def debug(self, queries, stream=None, stats: bool = True) -> dict:
+        """One retrieval with every intermediate (synchronises; parity checks only).
+        ``list_stats`` are the streaming pass's, so with ``stats`` short lists take
+        its route too; without, the call takes the route of ``__call__``."""
         qp, nq = self._marshal(queries)
         S = len(self.indices)
         dev = self.frame_ids.device
@@ -262,10 +264,12 @@ class Retriever:
             "mass_hist": torch.empty((S, hist), dtype=torch.float32, device=dev),
             "pool": torch.empty((S, pool), dtype=torch.int32, device=dev),
             "pool_n": torch.empty(S, dtype=torch.int32, device=dev),
-            "list_stats": torch.empty((S, NL, 2), dtype=torch.int32, device=dev),
         }
-        dbg = L.DebugOut(*(t[k].data_ptr() for k in ("topk_pos", "topk_score", "vote_hist", "mass_hist",
-                                                      "pool", "pool_n", "list_stats")))
+        if stats:
+            t["list_stats"] = torch.empty((S, NL, 2), dtype=torch.int32, device=dev)
+        dbg = L.DebugOut(*(t[k].data_ptr() if k in t else None
+                           for k in ("topk_pos", "topk_score", "vote_hist", "mass_hist",
+                                     "pool", "pool_n", "list_stats")))
         L.check(L.lib().ss_retrieve_debug(self._handles, S, qp, nq, C.byref(p), self._ws.data_ptr(),
                                           self._ws.numel(), _stream_handle(stream), self.frame_ids.data_ptr(),
                                           self.votes.data_ptr(), self.mass.data_ptr(), self.n_out.data_ptr(),

@@ -54,11 +54,11 @@ def make_pair(cfg, spec, keys, compress=None, n_recent=0, max_frames=None, max_r
     return gidx, oidx
 
 
-def debug_run(gidxs, queries, top_k, n_select, pool_mult=4, head_mode=0):
+def debug_run(gidxs, queries, top_k, n_select, pool_mult=4, head_mode=0, stats=True):
     P = _P()
     r = P.Retriever(gidxs, top_k, n_select, pool_mult, head_mode)
     qd = [[dev_bf16(q) for q in qs] for qs in queries]
-    return r.debug(qd)
+    return r.debug(qd, stats=stats)
 
 
 def c1():
@@ -150,14 +150,15 @@ def test_small_grid_handed_out_tail_covers_last_tiles():
 
 def test_selected_scores_have_the_recompute_bits():
     """Every path scores a row with the same arithmetic: the scores the retrieval
-    selects (query prep fused with the sample pass, then the streaming pass) are
-    bit-equal to the standalone prep and recompute kernels' scores of the same
-    rows, in both head modes."""
+    selects (query prep fused with the sample pass, then the streaming pass; query
+    prep fused with the scores of every row) are bit-equal to the standalone prep
+    and recompute kernels' scores of the same rows, in both head modes."""
     cfg, spec, q, keys = c1()
     gidx, _ = make_pair(cfg, spec, keys)
     qd = [dev_bf16(x) for x in q]
-    for head_mode, n_lists in ((0, cfg.n_layers * cfg.n_q_heads), (1, cfg.n_layers)):
-        out = debug_run([gidx], [q], cfg.top_k, cfg.n_select, head_mode=head_mode)
+    n_heads = cfg.n_layers * cfg.n_q_heads
+    for head_mode, n_lists, stats in ((0, n_heads, True), (0, n_heads, False), (1, cfg.n_layers, True)):
+        out = debug_run([gidx], [q], cfg.top_k, cfg.n_select, head_mode=head_mode, stats=stats)
         for j in range(n_lists):
             l, h = (j // cfg.n_q_heads, j % cfg.n_q_heads) if head_mode == 0 else (j, 0)
             full = gidx.debug_scores(qd, l, h, head_mode=head_mode).cpu().numpy()

@@ -42,11 +42,11 @@ def test_short_lists(L, Hq, Hk, d, F, T, k, score_mode):
     import paper_2609_02780_amd as P
     g, o, q = _stream(P, L, Hq, Hk, d, F, T, 3, k, 4, seed=F)
     r = P.Retriever([g], k, 4, score_mode=score_mode)
-    out = r.debug([[dev_bf16(x) for x in q]])
-    assert np.all(out["list_stats"][0, :, 1] == 0)
-    assert np.all(out["list_stats"][0, :, 0] >= min(k, F * T))
-    rep = staged_check(o, q, out, 0, k, 4, score_mode=score_mode)
-    assert rep.get("swaps", 0) == 0 or rep["max_rel_score_err"] <= 1e-3
+    out = r.debug([[dev_bf16(x) for x in q]], stats=False)
+    staged_check(o, q, out, 0, k, 4, score_mode=score_mode)
+    plain = r([[dev_bf16(x) for x in q]])
+    for key, t in zip(("frame_ids", "votes", "mass", "n_out"), plain):
+        assert np.array_equal(t.cpu().numpy().view(np.uint8), out[key].view(np.uint8)), key
 
 
 def test_unequal_batch_with_an_empty_stream():
@@ -57,16 +57,39 @@ def test_unequal_batch_with_an_empty_stream():
     parts = [_stream(P, 2, 6, 2, 64, F, T, nq, k, K, seed=i, recent=rec)
              for i, (F, T, nq, rec) in enumerate([(1500, 16, 1, 0), (4097, 1, 5, 0), (60, 5, 17, 0), (5, 2, 64, 1), (3, 4, 2, 3)])]
     r = P.Retriever([g for g, _, _ in parts], k, K)
-    out = r.debug([[dev_bf16(x) for x in q] for _, _, q in parts])
-    for s, (_, o, q) in enumerate(parts[:4]):
-        staged_check(o, q, out, s, k, K)
-    assert out["n_out"][4] == 0 and np.all(out["frame_ids"][4] == -1)
+    for stats in (False, True):
+        out = r.debug([[dev_bf16(x) for x in q] for _, _, q in parts], stats=stats)
+        for s, (_, o, q) in enumerate(parts[:4]):
+            staged_check(o, q, out, s, k, K)
+        assert out["n_out"][4] == 0 and np.all(out["frame_ids"][4] == -1)
+
+
+@pytest.mark.parametrize("S", [1, 40])
+@pytest.mark.parametrize("score_mode", [0, 1])
+def test_stats_are_the_streaming_pass(score_mode, S):
+    """Lists of 8,192 rows whose statistics are asked for: the counts are the
+    rows at or above the sample's cut-off (about the planner's expectation, more
+    than k), not those at or above the k-th score, in a workspace of the size
+    that the library asks for."""
+    import paper_2609_02780_amd as P
+    k = 40
+    g, o, q = _stream(P, 1, 2, 1, 64, 512, 16, 3, k, 4, seed=9)
+    m, _, cap, E = P.sample_plan(8192, k)
+    assert m < 8192 and E > 2 * k
+    r = P.Retriever([g] * S, k, 4, score_mode=score_mode)
+    out = r.debug([[dev_bf16(x) for x in q]] * S)
+    for s in {0, S - 1}:
+        stats = out["list_stats"][s]
+        assert np.all(stats[:, 1] == 0) and np.all(stats[:, 0] <= cap)
+        assert np.all(stats[:, 0] > k + k // 4), stats
+        staged_check(o, q, out, s, k, 4, score_mode=score_mode)
 
 
 @pytest.mark.parametrize("T,dup", [(16, 1), (16, 40), (16, 100000)])
 def test_routes_agree(T, dup):
-    """The same call with the preferred workspace and with one that has no room
-    for every row's score: lists, votes and masses bit for bit.  ``dup`` equal
+    """The same call on its own route, with a workspace that has no room for every
+    row's score, and with the streaming pass's statistics asked for: lists, votes
+    and masses bit for bit.  ``dup`` equal
     rows in a row make ties at the cut (with all rows equal the lists are rows
     0 .. k - 1, and more rows tie than either route keeps)."""
     import paper_2609_02780_amd as P
@@ -78,17 +101,20 @@ def test_routes_agree(T, dup):
     q = [dev_bf16(W.bf16_bits(rng.standard_normal((Hq, 2, d)).astype(np.float32)))]
     for score_mode in (0, 1):
         r = P.Retriever([g], k, K, score_mode=score_mode)
-        a = r.debug([q])
+        a = r.debug([q], stats=False)
         need = r.workspace_bytes([2])
         small = P.Retriever([g], k, K, score_mode=score_mode)
         small._ws = torch.empty(need - 256, dtype=torch.uint8, device="cuda")
         small.workspace_bytes = lambda n_q: 1
-        b = small.debug([q])
+        b = small.debug([q], stats=False)
+        c = small.debug([q])
         if dup > F * T:
             np.testing.assert_array_equal(a["topk_pos"][0], np.tile(np.arange(k), (Hq, 1)))
         keys = ["topk_pos", "vote_hist"] + (["frame_ids", "votes", "topk_score", "mass", "mass_hist"] if score_mode == 0 else [])
         for key in keys:
             assert np.array_equal(a[key].view(np.uint8), b[key].view(np.uint8)), key
+        for key in b:   # both the sampled route
+            assert np.array_equal(b[key].view(np.uint8), c[key].view(np.uint8)), key
         # probabilities: two fixed-point sums of the normaliser, 2^-40 apart per row, and fp32 exp and log
         np.testing.assert_allclose(a["topk_score"], b["topk_score"], rtol=4e-6)
         np.testing.assert_allclose(a["mass_hist"], b["mass_hist"], rtol=4e-6)
