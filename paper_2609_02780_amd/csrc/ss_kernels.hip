@@ -3548,10 +3548,18 @@ struct GramArgs {
   float* gram;          // [S][pool][ld]
 };
 
-// Quarter q of the dimensions of tile (ti, tj) of stream s's Gram matrix, from
+// Quarter w of the dimensions of tile (ti, tj) of stream s's Gram matrix, from
 // the pool's frame ids `ids` (pn of them): lane l holds tile rows 4 (l >> 4) + j,
 // column l & 15.
-template <int NST>   // 16-dimension steps per wave: dim / 64
+//
+// A diagonal tile has one set of rows.  Where one block walks all tiles of a
+// stream (k_pool_tail) not loading it twice pays: a pool of 32 at 512 elements
+// 36.7 -> 35.1 us a call; where every tile has its own block, reading both sets
+// in turn does, in 48 registers: a branch takes more of them the wider the
+// descriptor (74 at 512 elements, 128 with 10 spilled at 1,024) and a pool of 64
+// went from 46.3 to 47.0 us a call at 1,024 elements, from 45.9 to 46.0 at 512.
+enum class GramRows { kBoth, kBranch, kDiagonal };   // kDiagonal: ti == tj in every call
+template <int NST, GramRows ROWS>   // 16-dimension steps per wave: dim / 64
 __device__ __forceinline__ f32x4 gram_quarter(const GramArgs& a, int s, int ti, int tj, int pn, const int32_t* ids,
                                               int w) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -3562,14 +3570,22 @@ __device__ __forceinline__ f32x4 gram_quarter(const GramArgs& a, int s, int ti, 
   const float* xi = a.desc[s] + (size_t)ids[ri] * dim + w * (dim / 4) + 4 * (lane >> 4);
   const float* xj = a.desc[s] + (size_t)ids[rj] * dim + w * (dim / 4) + 4 * (lane >> 4);
   float4 va[NST], vb[NST];
+  if (ROWS == GramRows::kBoth) {
 #pragma unroll
-  for (int u = 0; u < NST; ++u) va[u] = *reinterpret_cast<const float4*>(xi + 16 * u);
-  if (ti != tj) {   // uniform; a diagonal tile has one set of rows
-#pragma unroll
-    for (int u = 0; u < NST; ++u) vb[u] = *reinterpret_cast<const float4*>(xj + 16 * u);
+    for (int u = 0; u < NST; ++u) {
+      va[u] = *reinterpret_cast<const float4*>(xi + 16 * u);
+      vb[u] = *reinterpret_cast<const float4*>(xj + 16 * u);
+    }
   } else {
 #pragma unroll
-    for (int u = 0; u < NST; ++u) vb[u] = va[u];
+    for (int u = 0; u < NST; ++u) va[u] = *reinterpret_cast<const float4*>(xi + 16 * u);
+    if (ROWS == GramRows::kBranch && ti != tj) {   // uniform
+#pragma unroll
+      for (int u = 0; u < NST; ++u) vb[u] = *reinterpret_cast<const float4*>(xj + 16 * u);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NST; ++u) vb[u] = va[u];
+    }
   }
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -3589,7 +3605,7 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int s, int ti, int 
                                           const int32_t* ids, float (*part)[256]) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
   if (w < 4) {
-    const f32x4 acc = gram_quarter<NST>(a, s, ti, tj, pn, ids, w);
+    const f32x4 acc = gram_quarter<NST, GramRows::kBoth>(a, s, ti, tj, pn, ids, w);
 #pragma unroll
     for (int j = 0; j < 4; ++j) part[w][(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
   }
@@ -3638,13 +3654,16 @@ __global__ __launch_bounds__(1024) void k_pool_gram(VoteArgs va, GramArgs a) {
 }
 
 // Pool, Gram matrix and max-min of a stream in one block, for pools of at most
-// kTailPool frames: few enough tiles that the block's four groups of four waves
+// tail_pool frames: few enough tiles that the block's four groups of four waves
 // form them about as fast as as many blocks, and the picks read the distances
 // from LDS, so that max-min's launch and its read of the matrix go away.  The
 // same sums in the same order as k_pool_gram's.
 constexpr int kTailPool = 32;
+constexpr int tail_pool(int dim) { return dim <= 512 ? kTailPool : 16; }
 template <int NST>
 __global__ __launch_bounds__(1024) void k_pool_tail(VoteArgs va, GramArgs a, MaxminArgs ma) {
+  // a pool of at most 16 frames is one tile
+  constexpr GramRows kRows = tail_pool(64 * NST) > 16 ? GramRows::kBranch : GramRows::kDiagonal;
   __shared__ PoolShared psh;
   __shared__ int32_t ids[kMaxPool];
   __shared__ float part[4][4][256];
@@ -3669,7 +3688,7 @@ __global__ __launch_bounds__(1024) void k_pool_tail(VoteArgs va, GramArgs a, Max
     while (ti < nt && left >= nt - ti) { left -= nt - ti; ++ti; }
     const int tj = ti + left;
     if (ti < nt) {   // the same for a group of waves
-      const f32x4 acc = gram_quarter<NST>(a, s, ti, tj, pn, ids, w & 3);
+      const f32x4 acc = gram_quarter<NST, kRows>(a, s, ti, tj, pn, ids, w & 3);
 #pragma unroll
       for (int j = 0; j < 4; ++j) part[grp][w & 3][(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
     }
@@ -5390,7 +5409,7 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
   // (1,024); of 32 at 256 elements 32.7 / 30.8, at 512 176.7 / 174.5 (the pool
   // half full) and 33.3 / 32.7 (full), but at 1,024 39.3 / 41.9, and of 64 at 512
   // 47.6 / 61.9: one CU's matrix cores and L2 reads take longer than the boundary.
-  const bool tail = pool_gram && (p.pool <= 16 || (p.pool <= kTailPool && ga.dim <= 512));
+  const bool tail = pool_gram && p.pool <= tail_pool(ga.dim);
   gram_launchers<kMaxDescDim / 64>()[ga.dim / 64 - 1](dim3(tail ? p.S : p.S * ga.tiles * ga.tiles),
                                                       pool_gram ? &va : nullptr, ga, tail ? &ma : nullptr, st);
   if (!tail) hipLaunchKernelGGL(k_maxmin, dim3(p.S), dim3(1024), 0, st, ma);
