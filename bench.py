@@ -8,9 +8,10 @@ votes, pool and max-min), with the index already resident in HBM.
 
 Prints one JSON line.  ``value`` is key vectors scored per second (a key vector
 is one stored d-dim bf16 row at one (layer, KV head); each is scored against
-its G query heads).  ``roofline`` covers the streaming scoring kernel, timed
-with HIP events recorded around it on the call's stream.  ``cpu_baseline`` is
-the CPU oracle timed on a bounded sample of the same workload.
+its G query heads).  ``roofline`` covers the scoring kernel (for lists short
+enough to be selected from every row's score that is the one that forms the
+query tiles too), timed with HIP events recorded around it on the call's
+stream.  ``cpu_baseline`` is the CPU oracle timed on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
@@ -35,7 +36,6 @@ KERNEL_SRC = os.path.join(ROOT, "paper_2609_02780_amd", "csrc", "ss_kernels.hip"
 # committed PMC summaries of the streaming kernel per (workload, score mode)
 TRAFFIC_FILES = {("C4", 0): "k_stream_c4_traffic.md", ("C5", 0): "k_stream_c5_traffic.md",
                  ("P4", 0): "k_stream_hm_p4_traffic.md", ("P4", 1): "k_stream_hp_p4_traffic.md"}
-HOT_KERNEL = "k_stream<128>"
 
 
 def log(*a):
@@ -346,10 +346,15 @@ def cpu_model() -> str:
     return "unknown"
 
 
-def hot_kernel(cfg, score_mode: int) -> str:
-    """The streaming scoring kernel of the workload's mode."""
+def hot_kernel(cfg, score_mode: int, rows) -> str:
+    """The scoring kernel of the workload's mode and sizes (``rows`` per stream), as
+    the library chooses it: batches of short per-head lists (at most 8,192 rows,
+    or 32,768 and 3 M scores in all) are scored with their query prep in one kernel."""
     if cfg.head_mode == 0:
-        return HOT_KERNEL
+        lists, n = len(rows) * cfg.n_layers * cfg.n_q_heads, max(rows)
+        short = (cfg.top_k <= 1024 and n <= 32768 and len(rows) * cfg.n_layers <= 128 and lists <= 512
+                 and (n <= 8192 or lists * n <= 3_000_000))
+        return f"k_score_all<{cfg.head_dim}>" if short else f"k_stream<{cfg.head_dim}>"
     if score_mode == 1:
         return f"k_stream_hp<{cfg.head_dim}, {cfg.n_kv_heads}>"
     return f"k_stream_hm<{cfg.head_dim}>"
@@ -502,7 +507,7 @@ def main():
         "p90_latency_ms": float(np.percentile(lat, 90)),
         "scores_per_s": value * cfg.group,
         "hbm_frac_end_to_end": key_bytes / (np.percentile(lat, 50) / 1e3) / 1e9 / HBM_PEAK_GBS,
-        "roofline": {"kernel": hot_kernel(cfg, args.score_mode), "bound": "hbm", "achieved": achieved,
+        "roofline": {"kernel": hot_kernel(cfg, args.score_mode, rows), "bound": "hbm", "achieved": achieved,
                      "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "avg_kernel_ms": float(hot.mean()), "bytes_per_launch": key_bytes,
