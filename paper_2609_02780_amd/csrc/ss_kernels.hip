@@ -4269,7 +4269,8 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
     const int pb = c & 1;
     const float v = avail ? val : -INFINITY;
     {
-      const uint32_t u = ord_u32(v), m1 = km_wave_max_u32(u);
+      // tokens taken, and lanes without one, stay below every value, a NaN included
+      const uint32_t u = avail ? ord_u32(val) : 0u, m1 = km_wave_max_u32(u);
       const uint64_t bm = __ballot(u == m1), nm = __ballot(v >= ord_f32(m1) - band);
       const int bl = __builtin_ctzll(bm);   // the lowest token of the wave's largest
       if (lane == bl) best[pb][w] = KmBest{m1, my_tok + ((nm & (nm - 1)) ? kKmNear : 0)};

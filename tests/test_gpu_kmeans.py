@@ -72,3 +72,26 @@ def test_kmeans_equal_tokens(copies, n_c):
     C, cnt, _ = O.kmeans(O.decode_bf16(bits[0]), n_c, 3)
     assert np.abs(rows[0, 0].astype(np.int32) - O.round_bf16(C).astype(np.int32)).max() <= 1
     np.testing.assert_array_equal(counts[0, 0], cnt)
+
+
+@pytest.mark.parametrize("bad", [0x7FC0, 0xFFC0, 0xFFFF, 0x7F80, 0xFF80])
+@pytest.mark.parametrize("T,n_c,d", [(17, 4, 64), (70, 16, 128), (196, 33, 128)])
+def test_kmeans_non_finite_tokens(T, n_c, d, bad):
+    """One NaN or infinity in a frame, of either sign: the mean and every distance
+    from it are NaN (or infinite), and the picks must still be distinct tokens of
+    the frame (the stored rows of no rounds at all); after rounds every token has
+    one centre."""
+    rng = np.random.default_rng(bad + T)
+    bits = W.bf16_bits(rng.standard_normal((1, 2 * T, d)).astype(np.float32))
+    bits[0, T // 2, 3] = bad
+    rows, _ = _compress(bits, T, n_c, 0)
+    tokens = {t.tobytes(): i for i, t in enumerate(bits[0, :T])}
+    picks = [tokens.get(r.tobytes(), -1) for r in rows[0, 0]]
+    assert min(picks) >= 0 and len(set(picks)) == n_c, picks
+    assert picks[0] in (0, T // 2)                  # equal distances from the mean, or the odd one's NaN above them
+    rows, counts = _compress(bits, T, n_c, 3)
+    assert np.all(counts.sum(axis=-1) == T)
+    C, cnt, dg = O.kmeans(O.decode_bf16(bits[0, T:]), n_c, 3)      # the other frame is untouched by it
+    if min(dg["init_margin"], dg["assign_margin"]) >= MARGIN:
+        assert np.abs(rows[0, 1].astype(np.int32) - O.round_bf16(C).astype(np.int32)).max() <= 1
+        np.testing.assert_array_equal(counts[0, 1], cnt)
