@@ -3745,8 +3745,8 @@ __device__ __forceinline__ void unit_desc(const AppendArgs& a, int f, float val,
   __syncthreads();
   double tot = 0.0;
   for (int i = 0; i < (int)blockDim.x / kWave; ++i) tot += red[i];
-  const double inv = tot > 0.0 ? 1.0 / sqrt(tot) : 0.0;
-  if (t < dim) a.dst.desc[(a.frame0 + f) * (int64_t)dim + t] = (float)((double)val * inv);
+  // a frame without a norm (all zeros, or a NaN among its keys) has a descriptor of zeros
+  if (t < dim) a.dst.desc[(a.frame0 + f) * (int64_t)dim + t] = tot > 0.0 ? (float)((double)val * (1.0 / sqrt(tot))) : 0.f;
   if (t == 0) {
     a.dst.frame_off[a.frame0 + f + 1] = (int32_t)(a.row0 + (int64_t)(f + 1) * a.rows_per_frame);
     if (f == 0) a.dst.frame_off[a.frame0] = (int32_t)a.row0;

@@ -57,3 +57,24 @@ def test_append_entries(L, Hk, d, T, compress):
     np.testing.assert_array_equal(offs, rpf * np.arange(F + 1))
     kmax = a[al(off + (F + 1) * 4):][:4].view(torch.float32).item()
     assert kmax == np.abs(X).max()
+
+
+@pytest.mark.parametrize("compress", [None, (4, 2)])
+@pytest.mark.parametrize("bad", [0x7FC0, 0xFFC0, None])
+def test_descriptor_of_a_frame_without_a_norm(bad, compress):
+    """A NaN among a frame's last-layer keys, or keys that are all zero: that
+    frame's descriptor is zeros, the others' are untouched."""
+    import paper_2609_02780_amd as P
+    rng = np.random.default_rng(3)
+    Hk, F, T, d = 2, 3, 9, 64
+    bits = W.bf16_bits(rng.standard_normal((Hk, F, T, d)).astype(np.float32))
+    if bad is None:
+        bits[:, 1] = 0
+    else:
+        bits[1, 1, 4, 7] = bad
+    g = P.ShallowIndex(1, Hk, Hk, d, F, F * T)
+    g.append([torch.from_numpy(bits.reshape(Hk, F * T, d).view(np.int16)).cuda()], F, T, compress)
+    desc = g.export()["desc"]
+    assert np.all(desc[1] == 0)
+    for f in (0, 2):
+        np.testing.assert_allclose(desc[f], O.descriptor(O.decode_bf16(bits[:, f])), atol=T * 2.0 ** -22)
