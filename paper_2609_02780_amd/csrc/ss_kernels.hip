@@ -4801,7 +4801,8 @@ __global__ __launch_bounds__(kWave) void k_cluster_assign(AbsorbArgs a) {
       if (join) {
         float inv = __builtin_amdgcn_rsqf(nrm2);
         inv = fmaf(inv * fmaf(-nrm2 * inv, inv, 1.f), 0.5f, inv);   // one Newton step
-        if (!(nrm2 > 1e-30f)) inv = nrm2 > 0.f ? 1.0f / sqrtf(nrm2) : 1.f;   // the norm of nothing stays zero
+        // without a norm (zeros, or a NaN) the mean stays as it is
+        if (!(nrm2 > 1e-30f)) inv = nrm2 > 0.f ? 1.0f / sqrtf(nrm2) : 1.0f / (float)(n + 1);
 #pragma unroll
         for (int k = 0; k < EPL; ++k) c[k] = w[k] * inv;
         if (lane == 0) {

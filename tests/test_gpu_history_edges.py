@@ -81,3 +81,26 @@ def test_compaction_chains(F, drop, T, d):
     off = at + al(F * lg * d * 4)
     offs = a[off:off + (F - drop + 1) * 4].view(torch.int32).cpu().numpy()
     np.testing.assert_array_equal(offs, T * np.arange(F - drop + 1))
+
+
+def test_centroid_without_a_norm():
+    """An infinite key in the second frame of a full set's only cluster: the
+    joined centroid has no norm and is the plain mean (n c + k) / (n + 1), a NaN
+    where the key was infinite."""
+    import paper_2609_02780_amd as P
+    rng = np.random.default_rng(4)
+    Hk, d, F, T = 2, 64, 3, 5
+    bits = W.bf16_bits(rng.standard_normal((1, Hk, F, T, d)).astype(np.float32))
+    bits[0, 1, 1, 2, 9] = 0x7F80
+    g = P.ShallowIndex(1, Hk, Hk, d, F, F * T)
+    g.append([torch.from_numpy(bits[0].reshape(Hk, F * T, d).view(np.int16)).cuda()], F, T)
+    desc = g.export()["desc"]
+    cl = P.LongClusters(g, T, 1, 0.5)
+    cl.absorb(F, F)
+    got = cl.export()
+    assert got["n_clusters"] == 1 and got["overflow"] and got["sizes"].tolist() == [F]
+    c = desc[0].astype(np.float64)
+    for n in (1, 2):
+        c = (n * c + desc[n].astype(np.float64)) / (n + 1)
+    assert np.isnan(got["centroids"][0, d + 9])
+    np.testing.assert_allclose(np.delete(got["centroids"][0], d + 9), np.delete(c, d + 9), atol=2.0 ** -21)
