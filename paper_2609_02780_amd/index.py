@@ -210,7 +210,8 @@ class Retriever:
         self._handles = L.ptr_array([x.handle.value for x in self.indices])
 
     def workspace_bytes(self, n_q) -> int:
-        nq = n_q if isinstance(n_q, C.Array) else (C.c_int32 * len(self.indices))(*n_q)
+        S = len(self.indices)
+        nq = n_q if isinstance(n_q, C.c_int32 * S) else (C.c_int32 * S)(*n_q)
         need = L.lib().ss_retrieve_workspace_bytes(self._handles, len(self.indices), nq, C.byref(self.params))
         if need == 0:
             raise L.SSError(L.SS_ERR_INVALID_ARGUMENT, L.lib().ss_last_error().decode())

@@ -191,6 +191,26 @@ def test_workspace_grows_with_batch(L):
         lib.ss_index_destroy(h)
 
 
+def test_workspace_bytes_takes_any_token_counts(L):
+    """Token counts as a list or as any ctypes array are taken element by element:
+    too few read no memory past the array, a wider integer type is converted."""
+    from paper_2609_02780_amd.index import Retriever
+    hs = [create(L) for _ in range(2)]
+    r = Retriever.__new__(Retriever)
+    r.indices = hs
+    r._handles = L.ptr_array([h.value for h in hs])
+    r.params = L.RetrieveParams(256, 16, 4, 0, 0)
+    want = r.workspace_bytes([8, 9])
+    for nq in ((8, 9), (C.c_int32 * 2)(8, 9), (C.c_int64 * 2)(8, 9), (C.c_uint16 * 2)(8, 9)):
+        assert r.workspace_bytes(nq) == want
+    with pytest.raises(L.SSError):
+        r.workspace_bytes((C.c_int32 * 1)(8))
+    with pytest.raises(IndexError):
+        r.workspace_bytes((C.c_int32 * 3)(8, 9, 10))
+    for h in hs:
+        L.lib().ss_index_destroy(h)
+
+
 def test_evidence_validation(L):
     """Host-side checks of ss_assemble_evidence; nothing is launched."""
     lib = L.lib()
