@@ -37,7 +37,8 @@ def _stream(P, L, Hq, Hk, d, F, T, nq, k, K, seed, recent=0):
 @pytest.mark.parametrize("L,Hq,Hk,d,F,T,k", [
     (1, 2, 1, 64, 1, 1, 5), (2, 4, 2, 64, 3, 5, 16), (1, 7, 1, 128, 16, 16, 200), (2, 4, 4, 64, 41, 25, 257),
     (1, 2, 1, 64, 256, 16, 1024), (1, 2, 1, 128, 241, 17, 64), (1, 4, 1, 64, 512, 16, 1000), (1, 2, 2, 64, 483, 17, 1),
-    (1, 2, 1, 64, 1024, 16, 512), (1, 2, 1, 128, 1639, 10, 33), (1, 2, 1, 64, 2048, 16, 700)])
+    (1, 2, 1, 64, 1024, 16, 512), (1, 2, 1, 128, 1639, 10, 33), (1, 2, 1, 64, 2048, 16, 700),
+    (1, 2, 1, 64, 2048, 16, 1024), (1, 2, 1, 128, 1200, 16, 960), (1, 2, 1, 64, 331, 25, 1024), (1, 2, 1, 64, 300, 15, 1024)])
 def test_short_lists(L, Hq, Hk, d, F, T, k, score_mode):
     import paper_2609_02780_amd as P
     g, o, q = _stream(P, L, Hq, Hk, d, F, T, 3, k, 4, seed=F)
@@ -47,6 +48,32 @@ def test_short_lists(L, Hq, Hk, d, F, T, k, score_mode):
     plain = r([[dev_bf16(x) for x in q]])
     for key, t in zip(("frame_ids", "votes", "mass", "n_out"), plain):
         assert np.array_equal(t.cpu().numpy().view(np.uint8), out[key].view(np.uint8)), key
+
+
+@pytest.mark.parametrize("score_mode", [0, 1])
+@pytest.mark.parametrize("n,above,tied,k", [(20000, 500, 6000, 1000), (32768, 1023, 9000, 1024), (9000, 0, 8990, 1000),
+                                            (20000, 999, 1, 1000), (8192, 100, 4200, 1024)])
+def test_many_ties_at_the_cut(n, above, tied, k, score_mode):
+    """``above`` rows over ``tied`` equal ones over the rest, k ending among the
+    equal ones: more rows reach the cut than are kept for the selection, from
+    the first bound and (k near the number of threads) from the closer one."""
+    import paper_2609_02780_amd as P
+    T = 8
+    rng = np.random.default_rng(n + above)
+    v = np.concatenate([2.0 + np.arange(above) / 64.0, np.ones(tied), -1.0 - rng.random(n - above - tied)])
+    x = np.zeros((1, n, 64), np.float32)
+    x[0, :, 5] = rng.permutation(v)
+    keys = [W.bf16_bits(x)]
+    q = np.zeros((2, 1, 64), np.float32)
+    q[0, 0, 5], q[1, 0, 5] = 1.0, 0.25
+    q = [W.bf16_bits(q)]
+    g = P.ShallowIndex(1, 2, 1, 64, n // T, n)
+    g.append([dev_bf16(keys[0])], n // T, T)
+    o = O.Index(1, 2, 1, 64)
+    o.append(keys, n // T, T)
+    out = P.Retriever([g], k, 4, score_mode=score_mode).debug([[dev_bf16(q[0])]], stats=False)
+    rep = staged_check(o, q, out, 0, k, 4, score_mode=score_mode)
+    assert rep.get("swaps", 0) == 0
 
 
 def test_unequal_batch_with_an_empty_stream():
