@@ -3577,12 +3577,14 @@ struct GramArgs {
 // the pool's frame ids `ids` (pn of them): lane l holds tile rows 4 (l >> 4) + j,
 // column l & 15.
 //
-// A diagonal tile has one set of rows.  Where one block walks all tiles of a
-// stream (k_pool_tail) not loading it twice pays: a pool of 32 at 512 elements
-// 36.7 -> 35.1 us a call; where every tile has its own block, reading both sets
-// in turn does, in 48 registers: a branch takes more of them the wider the
-// descriptor (74 at 512 elements, 128 with 10 spilled at 1,024) and a pool of 64
-// went from 46.3 to 47.0 us a call at 1,024 elements, from 45.9 to 46.0 at 512.
+// A diagonal tile has one set of rows.  Not loading it twice pays where one block
+// walks all tiles of a stream (k_pool_tail: a pool of 32 at 512 elements 36.7 ->
+// 35.1 us a call) and, up to 512 elements, a little where every tile has its own
+// block and there are few (10 and 41 frames 27.6 -> 27.4 and 33.3 -> 33.1 us; 250
+// frames and the 10-minute index the same).  Beyond, the branch holds all of both
+// sets at once (128 registers with 10 spilled at 1,024 elements, where reading
+// them in turn takes 48) and loses: a pool of 64 at 1,024 elements 47.1 -> 46.6 us
+// with 150 frames, 73.5 -> 72.2 with 400, without it.
 enum class GramRows { kBoth, kBranch, kDiagonal };   // kDiagonal: ti == tj in every call
 template <int NST, GramRows ROWS>   // 16-dimension steps per wave: dim / 64
 __device__ __forceinline__ f32x4 gram_quarter(const GramArgs& a, int s, int ti, int tj, int pn, const int32_t* ids,
@@ -3630,7 +3632,8 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int s, int ti, int 
                                           const int32_t* ids, float (*part)[256]) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
   if (w < 4) {
-    const f32x4 acc = gram_quarter<NST, GramRows::kBoth>(a, s, ti, tj, pn, ids, w);
+    constexpr GramRows kRows = NST <= 8 ? GramRows::kBranch : GramRows::kBoth;
+    const f32x4 acc = gram_quarter<NST, kRows>(a, s, ti, tj, pn, ids, w);
 #pragma unroll
     for (int j = 0; j < 4; ++j) part[w][(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
   }
