@@ -3888,9 +3888,12 @@ __global__ __launch_bounds__(kAppendThreads) void k_desc(AppendArgs a, int f_fir
 // Layout.  What bounds this kernel is the chain of dependent steps (one block
 // barrier per pick, two per round) and, with enough problems on a CU, the
 // matrix cores.  So a problem is a block of only four waves, two blocks share a
-// CU and fill each other's waits, and what never changes stays in registers:
-// wave w holds token tiles w, w + 4, w + 8, w + 12 (16 tokens each) as MFMA
-// operands and, transposed, all tokens of its own 8-dim chunks for the update.
+// CU and fill each other's waits (one, where more than 192 tokens go into more
+// than 48 centroids of 128 dims: 83 KB of LDS), and what never changes stays in
+// registers: wave w holds token tiles w, w + 4, w + 8, w + 12 (16 tokens each) as
+// MFMA operands and, transposed, all tokens of its own 8-dim chunks for the
+// update.  (Beyond 48 centroids of 128 dims one of the 16 transposed operands has
+// no room there and is read back for every centre tile.)
 // Lane (r, c) = (lane >> 4, lane & 15) owns token 16 (w + 4 r) + c.  LDS holds
 // the token rows until the picks are made, then in their place the centres'
 // operands and the one-hot membership.
@@ -3949,30 +3952,40 @@ __device__ __forceinline__ float bf16f(uint16_t h) { return __uint_as_float((uin
 typedef const __attribute__((address_space(3))) uint32_t* lds_u32;
 typedef const __attribute__((address_space(3))) u32x4* lds_u32x4;
 
-// Direct squared distance sum_e (x_e - y_e)^2 (fmaf in dimension order) of two
-// bf16 rows in LDS; 16 dims at a time are loaded ahead of the chain.
-template <int D>
-__device__ __forceinline__ float km_dist_rows(lds_u32 xr, lds_u32 yr) {
-  float acc = 0.f;
+// Smallest direct squared distance sum_e (x_e - y_e)^2 (fmaf in dimension order)
+// of a bf16 row in LDS to R others; 16 dims at a time are loaded ahead of the
+// chains.  One chain of 2 D dependent operations is nearly all latency: R of them
+// go side by side.
+template <int D, int R>
+__device__ __forceinline__ float km_dist_rows(lds_u32 xr, const lds_u32 (&yr)[R]) {
+  float acc[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) acc[i] = 0.f;
 #pragma unroll 1
   for (int c0 = 0; c0 < D / 8; c0 += 2) {
-    u32x4 xa[2], ya[2];
+    u32x4 xa[2], ya[R][2];
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       xa[v] = *(lds_u32x4)(xr + 4 * (c0 + v));
-      ya[v] = *(lds_u32x4)(yr + 4 * (c0 + v));
+#pragma unroll
+      for (int i = 0; i < R; ++i) ya[i][v] = *(lds_u32x4)(yr[i] + 4 * (c0 + v));
     }
 #pragma unroll
     for (int v = 0; v < 2; ++v)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float d0 = bf16_lo(xa[v][k]) - bf16_lo(ya[v][k]);
-        acc = fmaf(d0, d0, acc);
-        const float d1 = bf16_hi(xa[v][k]) - bf16_hi(ya[v][k]);
-        acc = fmaf(d1, d1, acc);
-      }
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          const float d0 = bf16_lo(xa[v][k]) - bf16_lo(ya[i][v][k]);
+          acc[i] = fmaf(d0, d0, acc[i]);
+          const float d1 = bf16_hi(xa[v][k]) - bf16_hi(ya[i][v][k]);
+          acc[i] = fmaf(d1, d1, acc[i]);
+        }
   }
-  return acc;
+  float m = acc[0];
+#pragma unroll
+  for (int i = 1; i < R; ++i) m = fminf(m, acc[i]);
+  return m;
 }
 
 // Exact (direct-form) minimum squared distance of a token to the first c picks,
@@ -3985,58 +3998,89 @@ __device__ __forceinline__ float km_exact_min(lds_u32 xs, lds_u32 chosen, int t0
   const int lane = threadIdx.x & 63;
   const bool two = c <= 32;
   const int p = two ? lane & 31 : lane;
-  float m = p < c ? km_dist_rows<D>(xs + (two && lane >= 32 ? t1 : t0) * XW, xs + chosen[p] * XW) : INFINITY;
+  float m = INFINITY;
+  if (p < c) {
+    const lds_u32 pick[1] = {xs + chosen[p] * XW};
+    m = km_dist_rows<D, 1>(xs + (two && lane >= 32 ? t1 : t0) * XW, pick);
+  }
 #pragma unroll
   for (int o = 1; o < 32; o <<= 1) m = fminf(m, __shfl_xor(m, o));
   if (!two) m = fminf(m, __shfl_xor(m, 32));
   return m;
 }
 
-// The same for one token per lane against picks p0 .. p1 - 1, from minimum m on:
-// where a wave holds many candidates (frames with many equal tokens), their
-// minima are carried from pick to pick.
-template <int D>
+// The same for one token per lane against picks p0 .. p1 - 1, R at a time, from
+// minimum m on: where near ties are frequent (many equal tokens, or a common
+// component much longer than what sets the tokens apart), every lane's minimum
+// is carried from pick to pick.
+template <int D, int R>
 __device__ __forceinline__ float km_exact_min_own(lds_u32 xs, lds_u32 chosen, int tok, int p0, int p1, float m) {
   constexpr int XW = KmLayout<D>::XW;
-  for (int p = p0; p < p1; ++p) m = fminf(m, km_dist_rows<D>(xs + tok * XW, xs + chosen[p] * XW));
+  int p = p0;
+  if (R > 1)
+    for (; p + 1 < p1; p += R) {
+      lds_u32 pick[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) pick[i] = xs + chosen[min(p + i, p1 - 1)] * XW;
+      m = fminf(m, km_dist_rows<D, R>(xs + tok * XW, pick));
+    }
+  for (; p < p1; ++p) {
+    const lds_u32 pick[1] = {xs + chosen[p] * XW};
+    m = fminf(m, km_dist_rows<D, 1>(xs + tok * XW, pick));
+  }
   return m;
 }
-constexpr int kKmFew = 6;   // candidates of a wave taken row by row (two at a time while c <= 32)
+constexpr int kKmFew = 6;     // candidates of a wave taken row by row (two at a time while c <= 32)
+constexpr int kKmPicks = 4;   // picks side by side where the minima are carried on
 
-// The nearest centre of a token row in the direct form, one lane per centre (the
-// centre is the exact sum of its parts), ties to the lower centre.  TWO (C <= 32):
-// two rows, one in each half of the wave; the result holds for the lane's half.
-template <int D, bool TWO>
-__device__ __forceinline__ int km_exact_nearest(lds_u32 rows, lds_u32x4 opA, int C) {
+// The nearest centres of token rows (D / 2 words apart) in the direct form, one
+// lane per centre (the centre is the exact sum of its parts), ties to the lower
+// centre.  TWO (C <= 32): row i of each half of the wave, R rows a half; the
+// result holds for the lane's half.  What it costs is one lane's chain of 2 D
+// operations, so R rows go through it side by side for little more than one.
+template <int D, bool TWO, int R>
+__device__ __forceinline__ void km_exact_nearest(lds_u32 rows, lds_u32x4 opA, int C, int (&best)[R]) {
   constexpr int KS = D / 32;
   const int lane = threadIdx.x & 63, c = TWO ? lane & 31 : lane;
-  lds_u32 row = rows + (TWO && lane >= 32 ? D / 2 : 0);
-  float acc = INFINITY;
+  lds_u32 row = rows + (TWO && lane >= 32 ? R * D / 2 : 0);
+  float acc[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) acc[i] = c < C ? 0.f : INFINITY;
   if (c < C) {
-    acc = 0.f;
     lds_u32x4 oc = opA + (c >> 4) * 3 * KS * 64 + (c & 15);
-#pragma unroll 2
+#pragma unroll TWO ? 2 : 1
     for (int q = 0; q < D / 8; ++q) {
-      const u32x4 x = *(lds_u32x4)(row + 4 * q);
       const int at = (q >> 2) * 64 + 16 * (q & 3);
       const u32x4 c1 = oc[at], c2 = oc[KS * 64 + at], c3 = oc[2 * KS * 64 + at];
+      u32x4 x[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) x[i] = *(lds_u32x4)(row + i * (D / 2) + 4 * q);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const float d0 = bf16_lo(x[k]) - (bf16_lo(c1[k]) + (bf16_lo(c2[k]) + bf16_lo(c3[k])));
-        acc = fmaf(d0, d0, acc);
-        const float d1 = bf16_hi(x[k]) - (bf16_hi(c1[k]) + (bf16_hi(c2[k]) + bf16_hi(c3[k])));
-        acc = fmaf(d1, d1, acc);
+        const float y0 = bf16_lo(c1[k]) + (bf16_lo(c2[k]) + bf16_lo(c3[k]));
+        const float y1 = bf16_hi(c1[k]) + (bf16_hi(c2[k]) + bf16_hi(c3[k]));
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          const float d0 = bf16_lo(x[i][k]) - y0;
+          acc[i] = fmaf(d0, d0, acc[i]);
+          const float d1 = bf16_hi(x[i][k]) - y1;
+          acc[i] = fmaf(d1, d1, acc[i]);
+        }
       }
     }
   }
-  int bi = c < C ? c : INT_MAX;
 #pragma unroll
-  for (int o = 1; o < (TWO ? 32 : 64); o <<= 1) {
-    const float v2 = __shfl_xor(acc, o);
-    const int i2 = __shfl_xor(bi, o);
-    if (v2 < acc || (v2 == acc && i2 < bi)) { acc = v2; bi = i2; }
-  }
-  return min(bi, C - 1);
+  for (int i = 0; i < R; ++i) best[i] = c < C ? c : INT_MAX;
+#pragma unroll
+  for (int o = 1; o < (TWO ? 32 : 64); o <<= 1)
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const float v2 = __shfl_xor(acc[i], o);
+      const int i2 = __shfl_xor(best[i], o);
+      if (v2 < acc[i] || (v2 == acc[i] && i2 < best[i])) { acc[i] = v2; best[i] = i2; }
+    }
+#pragma unroll
+  for (int i = 0; i < R; ++i) best[i] = min(best[i], C - 1);
 }
 
 // Row swaps (gfx950): km_swap16 leaves (a0, b0, a2, b2) in a and (a1, b1, a3,
@@ -4109,8 +4153,10 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
   constexpr int NCW = (NCT + WPK - 1) / WPK;     // centre tiles of one wave in the update
   constexpr int MAXS = kMaxTokensCompress / 32;
   constexpr float kNone = -3.0e38f;              // below every v
+  constexpr bool kTwo = NCT <= 2;                // near ties: two rows in the wave's halves, or more side by side
+  constexpr int kRowsHalf = kTwo ? 1 : 2, kRows = kTwo ? 2 : kRowsHalf;
   extern __shared__ __align__(16) unsigned char km_dyn[];
-  __shared__ __align__(16) uint32_t wrow[4][D];            // a wave's own two scratch rows
+  __shared__ __align__(16) uint32_t wrow[4][kRows * D / 2];   // a wave's own scratch rows
   __shared__ __align__(16) KmBest best[2][4], bestfix[4];
   __shared__ int chosen[kMaxCentroids];
   __shared__ float xn[kMaxTokensCompress];
@@ -4289,6 +4335,7 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
   float my_min = INFINITY;
   float ex_min = INFINITY;   // the lane's token's exact minimum over picks 0 .. ex_upto - 1
   int ex_upto = 0;
+  int ties = 0;              // picks so far that were near ties (the same in every wave)
   const float band = 2.5f * 5.9604645e-8f * xnmax * (float)(6 * D + 16);
   for (int c = 0; c < C; ++c) {
     const int pb = c & 1;
@@ -4327,11 +4374,20 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
           if (x > bv || (x == bv && tk < bt)) { bv = x; bt = tk; }
         };
         auto tok_of = [&](int at) { return 16 * (w + 4 * (at >> 4)) + (at & 15); };
-        if (__popcll(cand) > kKmFew) {
-          ex_min = km_exact_min_own<D>((lds_u32)xs, (lds_u32)chosen, min(my_tok, T - 1), ex_upto, c, ex_min);
+        // Beyond 32 centroids the picks go on for long enough that a few candidates
+        // at nearly every pick, one row after the other, cost more than one chain a
+        // pick in every wave.  64 frames of tokens around a common vector 16 times as
+        // long as their spread, rows alone / now (with two rows a re-decision in the
+        // assignment) / 16 waves a problem: 64 centroids 2,272 / 1,688 / 1,806 us, 56
+        // 1,902 / 1,440 / 1,607, 40 670 / 577 / 1,144.  With half that vector near
+        // ties are rarer and rows stay: 930 / 897 us at 64 centroids, 1,300 carried.
+        ++ties;
+        const bool often = NCT > 2 && 10 * ties >= 9 * c;
+        if (often || __popcll(cand) > kKmFew) {
+          ex_min = km_exact_min_own<D, NCT <= 2 ? 1 : kKmPicks>((lds_u32)xs, (lds_u32)chosen, min(my_tok, T - 1), ex_upto, c, ex_min);
           ex_upto = c;
           const uint32_t mine = (cand >> lane & 1) ? ord_u32(ex_min) : 0u, x = km_wave_max_u32(mine);
-          take(ord_f32(x), tok_of(__builtin_ctzll(__ballot(mine == x))));   // tokens rise with the lane
+          if (cand) take(ord_f32(x), tok_of(__builtin_ctzll(__ballot(mine == x))));   // tokens rise with the lane
           cand = 0;
         }
         while (cand) {
@@ -4452,7 +4508,8 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
     float b1[4], b2[4], cmax = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) b1[r] = b2[r] = kNone;
-#pragma unroll
+    // more than two tiles unrolled take more registers than there are
+#pragma unroll NCT <= 2 ? NCT : 1
     for (int ct = 0; ct < NCT; ++ct) {
       float hc[4];   // |c|^2 / 2 of centres 16 ct + 4 rg + j
       {
@@ -4526,19 +4583,21 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
       const bool tie = tok_ok && C > 1 && !(2.f * (b1[0] - b2[0]) > 2.5f * eps + 1.2207031e-4f * vm);
       uint64_t todo = __ballot(tie);
       while (todo) {   // direct form, one lane per centre
-        const int at0 = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        const int at1 = NCT <= 2 && todo ? __builtin_ctzll(todo) : at0;
-        put_row(wrow[w], at0);
-        if (NCT <= 2) {
-          put_row(wrow[w] + D / 2, at1);
-          todo &= todo - 1;   // stays 0 where there was no second one
+        int at[kRows], n[kRowsHalf];
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+          at[i] = todo ? __builtin_ctzll(todo) : at[0];
+          todo &= todo - 1;   // stays 0 where there are no more
+          put_row(wrow[w] + i * (D / 2), at[i]);
         }
         km_wave_sync();
-        const int n = km_exact_nearest<D, NCT <= 2>((lds_u32)wrow[w], (lds_u32x4)opA, C);
+        km_exact_nearest<D, kTwo, kRowsHalf>((lds_u32)wrow[w], (lds_u32x4)opA, C, n);
         km_wave_sync();
-        const int n0 = __builtin_amdgcn_readlane(n, 0), n1 = __builtin_amdgcn_readlane(n, 32);
-        as = lane == at0 ? n0 : NCT <= 2 && lane == at1 ? n1 : as;
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+          const int m = __builtin_amdgcn_readlane(n[i % kRowsHalf], i < kRowsHalf ? 0 : 32);
+          as = lane == at[i] ? m : as;
+        }
       }
     }
     if (tok_ok) {
@@ -4553,6 +4612,7 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
     __syncthreads();
     if (!changed[ib]) break;   // the centres stay, and with them every later round
     // ---- update
+    const lds_u32x4 hot_lane = (lds_u32x4)hot + cw * 64 + lane;   // the lane's operands, constant distances apart
 #pragma unroll
     for (int i = 0; i < NCW; ++i) {
       const int ct = cw + i * WPK;
@@ -4561,7 +4621,7 @@ __global__ __launch_bounds__(kKmThreads, 2) void k_kmeans(AppendArgs a) {
 #pragma unroll
       for (int st = 0; st < MAXS; ++st)
         if (st < nsteps) {   // wave-uniform
-          const u32x4 oh = *reinterpret_cast<const u32x4*>(hot + (size_t)((st * NCT + ct) * 64 + lane) * 16);
+          const u32x4 oh = hot_lane[(st * NCT + i * WPK) * 64];
           s0 = mfma_bf16(xT[0][st], oh, s0);
           s1 = mfma_bf16(xT[1][st], oh, s1);
         }
