@@ -166,13 +166,6 @@ __device__ __forceinline__ f32x4 hm_finish(f32x4 v) {
 }
 #undef SS_DPP_F
 
-// Exclusive prefix count of `p` among the lanes of a wave.
-__device__ __forceinline__ int wave_excl_count(bool p) {
-  const uint64_t m = __ballot(p);
-  const int lane = threadIdx.x & (kWave - 1);
-  return __popcll(m & ((1ull << lane) - 1ull));
-}
-
 // Inclusive prefix sum over the lanes of a wave (lane 0 first): DPP row_shr
 // steps of 1, 2, 4 and 8 within each row of 16 lanes, then the totals of the
 // rows below, read from lanes 15, 31 and 47.
@@ -231,17 +224,6 @@ __device__ int block_argmax(float v, int idx, float* shv, int* shi) {
   }
   __syncthreads();
   return bi;
-}
-
-__device__ float block_max(float v, float* sh) {
-  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  if (lane == 0) sh[w] = v;
-  __syncthreads();
-  float r = sh[0];
-  for (int i = 1; i < nw; ++i) r = fmaxf(r, sh[i]);
-  __syncthreads();
-  return r;
 }
 
 // Wave 0 finds, in a 256-bin histogram scanned from the top bin down, the bin
@@ -404,22 +386,6 @@ __device__ void bitonic_desc_u64(uint64_t* a, int n) {
 
 __device__ __forceinline__ bool rec_less(uint64_t ah, uint64_t al, uint64_t bh, uint64_t bl) {
   return ah < bh || (ah == bh && al < bl);
-}
-
-// Descending bitonic sort of n (power of two) 128-bit records (hi, lo) in LDS.
-__device__ void bitonic_desc_u128(uint64_t* hi, uint64_t* lo, int n) {
-  for (int k = 2; k <= n; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < (n >> 1); i += blockDim.x) {
-        const int a = 2 * j * (i / j) + (i % j), b = a + j;
-        const bool desc = (a & k) == 0;
-        const uint64_t xh = hi[a], xl = lo[a], yh = hi[b], yl = lo[b];
-        const bool sw = desc ? rec_less(xh, xl, yh, yl) : rec_less(yh, yl, xh, xl);
-        if (sw) { hi[a] = yh; lo[a] = yl; hi[b] = xh; lo[b] = xl; }
-      }
-      __syncthreads();
-    }
-  }
 }
 
 __device__ __forceinline__ int pow2_ceil(int x) {
@@ -4110,10 +4076,6 @@ __device__ __forceinline__ void km_best2(float& a1, float& a2, float b1, float b
   a1 = fmaxf(a1, b1);
 }
 template <int ctrl>
-__device__ __forceinline__ float km_dpp_f(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xF, 0xF, false));
-}
-template <int ctrl>
 __device__ __forceinline__ uint32_t km_mov_dpp(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
 }
@@ -5249,11 +5211,10 @@ hipError_t launch_stream_hp(const ScoreArgs& a, const RetrievePlan& p, int64_t t
 
 // Blocks of k_score_all: the tiles of all lists' groups in slices of equal size,
 // at least one slice a group and one tile a wave, at most one block a CU.
-int plan_all_blocks(const RetrievePlan& p, AllArgs& a) {
-  constexpr int kCus = 256;
+int plan_all_blocks(const RetrievePlan& p, int cus, AllArgs& a) {
   int64_t tiles = 0;
   for (int s = 0; s < p.S; ++s) tiles += (int64_t)p.L * p.Hk * cdiv(p.st[s].n, kTile);
-  int per = std::max(p.D / 8, cdiv(tiles, kCus)), blocks = 0;
+  int per = std::max(p.D / 8, cdiv(tiles, cus)), blocks = 0;
   for (;;) {
     blocks = 0;
     for (int s = 0; s < p.S; ++s) {
@@ -5262,7 +5223,7 @@ int plan_all_blocks(const RetrievePlan& p, AllArgs& a) {
       blocks += p.L * p.Hk * a.spg[s];
     }
     a.blk_base[p.S] = blocks;
-    if (blocks <= kCus || blocks == p.S * p.L * p.Hk) break;
+    if (blocks <= cus || blocks == p.S * p.L * p.Hk) break;
     per += (per + 3) / 4;
   }
   return blocks;
@@ -5298,7 +5259,7 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
   // (450.2 -> 456.3 us)
   const bool all = p.all_rows;
   AllArgs aa{};
-  const int all_blocks = all ? plan_all_blocks(p, aa) : 0;
+  const int all_blocks = all ? plan_all_blocks(p, cus, aa) : 0;
   const bool pt = !all && D == 128 && p.head_mode == 0 && !p.hm_prob && pairs <= 128 && lists <= cus && p.m_max <= 2048;
   ps.xcd_map = cus == 256 && ps_blocks % 8 == 0;
   const bool fused = !all && !pt && prep_hm == 0 && pairs <= 128 && ps_blocks <= cus;
