@@ -332,6 +332,11 @@ void build_plan(ss::RetrievePlan& p, ss_index* const* idx, int s0, int S, const 
   // 30.6 us, 8,192 rows 45.4 / 37.5, 19,200 rows 51.8 / 47.5; 160 lists (8 KV
   // heads) of 16,384 rows 66.7 / 64.0, of 25,600 (4.1 M) 81.2 / 84.0; 448 lists of
   // 8,192 rows 84 / 65, of 19,200 107 / 110.
+  // The line at 512 lists holds for every list length up to 8,192 rows on this
+  // side of it; on the other it depends on the length: 896 lists of 3,920 rows 108
+  // / 67 us, of 7,840 98 / 95, 1,792 of 3,920 180 / 113, of 7,840 156 / 170, 3,360
+  // of 7,840 277 / 315.  A line on the scores there (shorter lists than about 4,096
+  // rows in any number) would gain what these say.
   const int64_t lists = (int64_t)p.S * p.NL;
   if (prm->head_mode == 0 && prm->top_k <= ss::kAllTopK && n_max <= ss::kAllRows && p.S * p.L <= 128 &&
       lists <= 512 && (n_max <= 8192 || lists * n_max <= 3'000'000)) {

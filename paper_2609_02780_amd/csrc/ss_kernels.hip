@@ -2144,12 +2144,13 @@ __global__ __launch_bounds__(1024) void k_prep_thresh(PrepArgs pa, PtArgs a) {
 // which cost the more the more waves take part, so a small sample gets four
 // waves with 8 slots a thread instead of sixteen with four, most of them empty
 // (whole call, 4 streams x 112 lists of 60,000 rows, m = 547: 202.8 -> 200.7
-// us).  With more than two lists per CU (`dense`) four waves also win on larger
-// samples, for more lists then share a CU: 8 x 96 lists of 176,400 rows (m =
-// 1,608) 717 -> 713 us, 16 ragged streams (m up to 6,430) 1,529.3 -> 1,527.8.
-// With fewer lists a larger sample wants the sixteen waves' loads and counting
-// (1,024-second index, 112 lists, attention probabilities: 174.6 us a call,
-// 176.0 with four waves of 16 slots).
+// us; 8 x 96 lists of 176,400 rows, m = 1,608: 717 -> 713).  With more than two
+// lists per CU (`dense`) four waves also win on larger samples, for more lists
+// then share a CU.  The kernel itself, 576 lists, sixteen waves at two blocks a
+// CU / four waves: m = 3,420 12.2 / 9.8 us, m = 5,470 14.3 / 13.2.  With fewer
+// lists a larger sample wants the sixteen waves' loads and counting (1,024-second
+// index, 112 lists, attention probabilities: 174.6 us a call, 176.0 with four
+// waves of 16 slots).
 void launch_thresh(const ListArgs& la, int lists, int m_max, bool dense, hipStream_t st) {
   const dim3 g(lists), b(1024), b4(256);
   if (m_max <= 2048) {
