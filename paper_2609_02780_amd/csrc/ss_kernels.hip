@@ -3090,7 +3090,7 @@ struct VoteArgs {
 // returns pn.  One block of 1024 threads per stream.
 constexpr int kVoteBins = 2048;   // vote histogram bins (the last one collects larger counts)
 constexpr int kTieRank = 128;     // frames tied at the cut ranked by counting
-constexpr int kVoteRank = 128;    // voted frames up to which all are ranked by counting
+constexpr int kVoteRank = 160;    // voted frames up to which all are ranked by counting
 
 struct PoolShared {
   uint64_t shi[kPoolSort];
@@ -3187,11 +3187,13 @@ __device__ int pool_select(const VoteArgs& a, int s, PoolShared& sh, int* lds_id
   // threads a record), instead of histogram, cut and gather.  Every block of
   // k_pool_gram does it, and with more frames a thread's walk over the records
   // takes longer than the three steps.  Per call, steps / counting, by voted
-  // frames (28 query heads, 64 of them in the pool): 100 34.8 / 33.6 us, 150 36.2 /
-  // 36.8, 200 38.9 / 40.2, 250 41.0 / 43.4 (8 KV heads: 54.9 / 57.9); the
-  // compressed 10-minute index 46.8 / 44.5.
+  // frames (28 query heads, 64 of them in the pool): 100 34.8 / 33.6 us, 140 36.5 /
+  // 36.4, 180 38.3 / 39.1, 200 38.9 / 40.2, 250 41.0 / 43.4.  Where few votes make
+  // many ties the steps take longer: the compressed 10-minute index (about 100 to
+  // 160 voted) 46.8 us by the steps alone, 44.9 with counting up to 128, 44.7 up to
+  // 160.
   if (n_voted <= kVoteRank) {
-    const int lg = n_voted <= 64 ? 6 : 7;
+    const int lg = n_voted <= 64 ? 6 : n_voted <= 128 ? 7 : 8;
     const int parts = 1024 >> lg, i = (int)threadIdx.x / parts, part = (int)threadIdx.x & (parts - 1);
     uint64_t h = 0, l = 0;
     int rank = 0;
