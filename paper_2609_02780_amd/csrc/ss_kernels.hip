@@ -1232,8 +1232,15 @@ struct AllArgs {
   int32_t* votes_g;
   int64_t* massfx_g;
 };
+// Questions of more tokens get their B tiles from k_prep: every slice would walk
+// all tokens, with half the loads in flight.  Per call, sampled route / here
+// without k_prep / with it, 112 lists of 11,760 rows: 1,024
+// tokens 75.8 / 75.1 / 69.9 us, 2,048 109.4 / 115.5 / 103.8, 4,096 194.8 / 227.8 /
+// 192.7; of 25,480 rows 84.1 / 86.5 / 81.6, 117.8 / 126.6 / 115.3, 202.6 / 237.7 /
+// 204.2; at 512 tokens 59.7 / 55.0 and 67.8 / 66.5 without it.
+constexpr int kAllPrepTokens = 768;
 
-template <int D>
+template <int D, bool PREPPED>   // PREPPED: the B tiles are there already
 __global__ __launch_bounds__(8 * D) void k_score_all(PrepArgs pa, ScoreArgs a, AllArgs ps) {
   constexpr int CPR = D / 8, TCH = 16 * CPR, NI = TCH / kWave, KS = D / 32;
   constexpr int NW = 8 * D / kWave;   // waves per block
@@ -1276,7 +1283,12 @@ __global__ __launch_bounds__(8 * D) void k_score_all(PrepArgs pa, ScoreArgs a, A
   u32x4 V[PF][NI];
 #pragma unroll
   for (int p = 0; p < PF; ++p) load(t0 + wave + NW * p, V[p]);
-  prep_b<D, 8>(pa, s * a.L + l, g, sh.part, bsh, slice == 0);   // (16 loads in flight would spill)
+  if (PREPPED) {
+    if (threadIdx.x < 2 * KS * kWave)
+      bsh[threadIdx.x] = pa.qB[((size_t)(s * a.L + l) * a.Hk + g) * (2 * KS * kWave) + threadIdx.x];
+  } else {
+    prep_b<D, 8>(pa, s * a.L + l, g, sh.part, bsh, slice == 0);   // (16 loads in flight would spill)
+  }
   __syncthreads();   // the B tile is in LDS and the partial sums are read no more
   u32x4* lt_ = sh.tiles[wave];
   u32x4 bh[KS], bl[KS];
@@ -5269,6 +5281,7 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
   int nq_max = 0;
   for (int s = 0; s < p.S; ++s) nq_max = std::max(nq_max, p.st[s].nq);
   const bool hm_prep = prep_hm == 1 && pairs <= 128 && p.Hk <= 8 && p.G * nq_max <= kHmPrepTerms;
+  const bool all_prepped = all && nq_max > kAllPrepTokens;
   PrepArgs pa_fused{};
   for (int first = 0; first < pairs; first += 128) {
     PrepArgs a{};
@@ -5281,9 +5294,8 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
     for (int s = 0; s < p.S; ++s) { a.nq[s] = p.st[s].nq; a.qscale[s] = p.st[s].qscale; }
     a.qB = reinterpret_cast<u32x4*>(p.qB);
     a.qcol = p.qcol;
-    if (fused || pt || hm_prep || all)
-      pa_fused = a;
-    else
+    if (fused || pt || hm_prep || all) pa_fused = a;
+    if (!(fused || pt || hm_prep || all) || all_prepped)
       hipLaunchKernelGGL(k_prep<D>, dim3(cnt * p.Hk), dim3(8 * D), 0, st, a);
   }
   ListArgs la{};
@@ -5314,7 +5326,8 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
     aa.massfx_g = p.massfx;
     for (int s = 0; s < p.S; ++s) aa.f[s] = p.st[s].f;
     if (p.ev_start) (void)hipEventRecord(p.ev_start, st);
-    hipLaunchKernelGGL(k_score_all<D>, dim3(all_blocks), dim3(8 * D), 0, st, pa_fused, a, aa);
+    if (all_prepped) hipLaunchKernelGGL((k_score_all<D, true>), dim3(all_blocks), dim3(8 * D), 0, st, pa_fused, a, aa);
+    else hipLaunchKernelGGL((k_score_all<D, false>), dim3(all_blocks), dim3(8 * D), 0, st, pa_fused, a, aa);
   } else if (pt) {
     PtArgs t{};
     t.NL = p.NL; t.L = p.L; t.Hq = p.Hq; t.Hk = p.Hk; t.G = p.G; t.f_max = p.f_max;

@@ -22,6 +22,25 @@ def _gpu():
 from parity import dev_bf16, staged_check  # noqa: E402
 
 
+@pytest.mark.parametrize("score_mode", [0, 1])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("nqs", [(768,), (769,), (4096,), (3, 1000, 1)])
+def test_long_questions(nqs, d, score_mode):
+    """Questions around the token count from which the query tiles are formed by a
+    kernel of their own, and a batch that mixes them with short ones; both routes."""
+    import paper_2609_02780_amd as P
+    k, K = 50, 5
+    parts = [_stream(P, 2, 6, 2, d, 70 + 9 * i, 13, nq, k, K, seed=i) for i, nq in enumerate(nqs)]
+    r = P.Retriever([g for g, _, _ in parts], k, K, score_mode=score_mode)
+    outs = [r.debug([[dev_bf16(x) for x in q] for _, _, q in parts], stats=stats) for stats in (False, True)]
+    for s, (_, o, q) in enumerate(parts):
+        for out in outs:
+            staged_check(o, q, out, s, k, K, score_mode=score_mode)
+        np.testing.assert_array_equal(outs[0]["topk_pos"][s], outs[1]["topk_pos"][s])
+        if score_mode == 0:
+            assert np.array_equal(outs[0]["topk_score"][s].view(np.uint32), outs[1]["topk_score"][s].view(np.uint32))
+
+
 def _stream(P, L, Hq, Hk, d, F, T, nq, k, K, seed, recent=0):
     cfg = W.Config("short", L, Hq, Hk, d, T, nq, k, K, n_frames=F, n_planted=1)
     spec = W.stream_specs(cfg)[0]
