@@ -2937,7 +2937,8 @@ __device__ void select_list(const ListArgs& a, int list, SelectShared& sh, uint3
 // Measured at 19,200 rows: 9.5 us (loads 2.7, bound and compaction 2.9, selection
 // 2.4), against about 17 us with radix rounds over all 32 slots a thread.
 constexpr int kAllKeep = 4096;   // rows kept by the bound (they take the place of the frame sums)
-template <int N>
+constexpr int kAllCloserK = 640; // k from which on a closer bound may be needed
+template <int N, bool CLOSER>
 __global__ __launch_bounds__(1024) void k_select_all(ListArgs a) {
   __shared__ SelectShared sh;
   __shared__ uint32_t hist[kSelHist];
@@ -3023,12 +3024,13 @@ __global__ __launch_bounds__(1024) void k_select_all(ListArgs a) {
       }
     __syncthreads();
     kept = (int)nkeep;
-    if (N == 4 || kept <= kAllKeep || round > 0 || bound >= mx) break;   // the same for the whole block
+    if (!CLOSER || kept <= kAllKeep || round > 0 || bound >= mx) break;   // the same for the whole block
     // k near the number of threads: most of their maxima count and the bound is a
     // low one; the same step over every row at or above it gives a closer one.
     // (k = 1,024, without it / with it / sampled route: 112 lists of 26,656 rows
     // 87.5 / 61.2 / 70.5 us a call, of 19,208 67.3 / 53.2 / 65.5, 8 of 32,000 65.3 /
-    // 41.8 / 53.7.)
+    // 41.8 / 53.7; at k = 768 52.5 / 47.9 / 57.3 with 19,208 rows, up to 640 the
+    // first bound does, and carrying this along costs 0.1 to 0.2 us.)
     uint32_t* wide = hist + 512;
     __syncthreads();   // nkeep has been read
     for (int i = threadIdx.x; i < kSelHist - 512; i += 1024) wide[i] = 0;
@@ -5450,10 +5452,19 @@ hipError_t retrieve_impl(RetrievePlan& p, hipStream_t st) {
     hipLaunchKernelGGL(k_select_hp<D>, dim3(lists), dim3(1024), 0, st, la);
   }
   else if (all) {
-    if (p.m_max <= 4096) hipLaunchKernelGGL(k_select_all<4>, dim3(lists), dim3(1024), 0, st, la);
-    else if (p.m_max <= 8192) hipLaunchKernelGGL(k_select_all<8>, dim3(lists), dim3(1024), 0, st, la);
-    else if (p.m_max <= 16384) hipLaunchKernelGGL(k_select_all<16>, dim3(lists), dim3(1024), 0, st, la);
-    else hipLaunchKernelGGL(k_select_all<32>, dim3(lists), dim3(1024), 0, st, la);
+    // (lists of at most 4,096 rows fit the kept ones)
+    const bool closer = p.k_max > kAllCloserK;
+    if (p.m_max <= 4096) hipLaunchKernelGGL((k_select_all<4, false>), dim3(lists), dim3(1024), 0, st, la);
+    else if (p.m_max <= 8192) {
+      if (closer) hipLaunchKernelGGL((k_select_all<8, true>), dim3(lists), dim3(1024), 0, st, la);
+      else hipLaunchKernelGGL((k_select_all<8, false>), dim3(lists), dim3(1024), 0, st, la);
+    } else if (p.m_max <= 16384) {
+      if (closer) hipLaunchKernelGGL((k_select_all<16, true>), dim3(lists), dim3(1024), 0, st, la);
+      else hipLaunchKernelGGL((k_select_all<16, false>), dim3(lists), dim3(1024), 0, st, la);
+    } else {
+      if (closer) hipLaunchKernelGGL((k_select_all<32, true>), dim3(lists), dim3(1024), 0, st, la);
+      else hipLaunchKernelGGL((k_select_all<32, false>), dim3(lists), dim3(1024), 0, st, la);
+    }
   } else if (lists > 2 * cus) hipLaunchKernelGGL(k_select_dense<D>, dim3(lists), dim3(1024), 0, st, la);
   else hipLaunchKernelGGL(k_select<D>, dim3(lists), dim3(1024), 0, st, la);
   // 8. Gram matrix, 9. max-min
