@@ -3560,16 +3560,16 @@ struct GramArgs {
 // the pool's frame ids `ids` (pn of them): lane l holds tile rows 4 (l >> 4) + j,
 // column l & 15.
 //
-// A diagonal tile has one set of rows.  Not loading it twice pays where one block
-// walks all tiles of a stream (k_pool_tail: a pool of 32 at 512 elements 36.7 ->
-// 35.1 us a call) and, up to 512 elements, a little where every tile has its own
-// block and there are few (10 and 41 frames 27.6 -> 27.4 and 33.3 -> 33.1 us; 250
-// frames and the 10-minute index the same).  Beyond, the branch holds all of both
-// sets at once (128 registers with 10 spilled at 1,024 elements, where reading
-// them in turn takes 48) and loses: a pool of 64 at 1,024 elements 47.1 -> 46.6 us
-// with 150 frames, 73.5 -> 72.2 with 400, without it.
-enum class GramRows { kBoth, kBranch, kDiagonal };   // kDiagonal: ti == tj in every call
-template <int NST, GramRows ROWS>   // 16-dimension steps per wave: dim / 64
+// A diagonal tile has one set of rows and is not loaded twice.  The loads of
+// kGramSteps steps are in flight together: all 16 of a 1,024-element quarter
+// spilled (128 registers, 10 spilled; 80 now), and reading both sets in turn, in 48
+// registers, waited for too many round trips.  Per call, 8 x 128 descriptors, all
+// at once / in turn / eight steps: 60 frames, pool of 32 49.2 / 49.9 / 49.0 us;
+// pool of 64 with 150, 250, 400 frames 47.0 / 46.5 / 46.6, 58.4 / 55.3 / 55.4 (the
+// ranking's change included), 73.0 / 72.3 / 72.5.  At 512 elements all is eight
+// steps: a pool of 32 35.2 us, 36.7 in turn.
+constexpr int kGramSteps = 8;
+template <int NST, bool DIAGONAL = false>   // 16-dimension steps per wave: dim / 64; DIAGONAL: ti == tj in every call
 __device__ __forceinline__ f32x4 gram_quarter(const GramArgs& a, int s, int ti, int tj, int pn, const int32_t* ids,
                                               int w) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -3579,31 +3579,33 @@ __device__ __forceinline__ f32x4 gram_quarter(const GramArgs& a, int s, int ti, 
   const int ri = min(ti * 16 + (lane & 15), pn - 1), rj = min(tj * 16 + (lane & 15), pn - 1);
   const float* xi = a.desc[s] + (size_t)ids[ri] * dim + w * (dim / 4) + 4 * (lane >> 4);
   const float* xj = a.desc[s] + (size_t)ids[rj] * dim + w * (dim / 4) + 4 * (lane >> 4);
-  float4 va[NST], vb[NST];
-  if (ROWS == GramRows::kBoth) {
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  const bool both = !DIAGONAL && ti != tj;   // uniform
 #pragma unroll
-    for (int u = 0; u < NST; ++u) {
-      va[u] = *reinterpret_cast<const float4*>(xi + 16 * u);
-      vb[u] = *reinterpret_cast<const float4*>(xj + 16 * u);
-    }
-  } else {
+  for (int u0 = 0; u0 < NST; u0 += kGramSteps) {
+    constexpr int C = NST < kGramSteps ? NST : kGramSteps;
+    float4 va[C], vb[C];
 #pragma unroll
-    for (int u = 0; u < NST; ++u) va[u] = *reinterpret_cast<const float4*>(xi + 16 * u);
-    if (ROWS == GramRows::kBranch && ti != tj) {   // uniform
+    for (int u = 0; u < C; ++u)
+      if (u0 + u < NST) va[u] = *reinterpret_cast<const float4*>(xi + 16 * (u0 + u));
+    if (both) {
 #pragma unroll
-      for (int u = 0; u < NST; ++u) vb[u] = *reinterpret_cast<const float4*>(xj + 16 * u);
+      for (int u = 0; u < C; ++u)
+        if (u0 + u < NST) vb[u] = *reinterpret_cast<const float4*>(xj + 16 * (u0 + u));
     } else {
 #pragma unroll
-      for (int u = 0; u < NST; ++u) vb[u] = va[u];
+      for (int u = 0; u < C; ++u)
+        if (u0 + u < NST) vb[u] = va[u];
     }
-  }
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int u = 0; u < NST; ++u) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].x, vb[u].x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].y, vb[u].y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].z, vb[u].z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].w, vb[u].w, acc, 0, 0, 0);
+    for (int u = 0; u < C; ++u) {
+      if (u0 + u >= NST) continue;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].x, vb[u].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].y, vb[u].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].z, vb[u].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u].w, vb[u].w, acc, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // the next steps' loads stay behind
   }
   return acc;
 }
@@ -3615,8 +3617,7 @@ __device__ __forceinline__ void gram_tile(const GramArgs& a, int s, int ti, int 
                                           const int32_t* ids, float (*part)[256]) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
   if (w < 4) {
-    constexpr GramRows kRows = NST <= 8 ? GramRows::kBranch : GramRows::kBoth;
-    const f32x4 acc = gram_quarter<NST, kRows>(a, s, ti, tj, pn, ids, w);
+    const f32x4 acc = gram_quarter<NST>(a, s, ti, tj, pn, ids, w);
 #pragma unroll
     for (int j = 0; j < 4; ++j) part[w][(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
   }
@@ -3673,8 +3674,7 @@ constexpr int kTailPool = 32;
 constexpr int tail_pool(int dim) { return dim <= 512 ? kTailPool : 16; }
 template <int NST>
 __global__ __launch_bounds__(1024) void k_pool_tail(VoteArgs va, GramArgs a, MaxminArgs ma) {
-  // a pool of at most 16 frames is one tile
-  constexpr GramRows kRows = tail_pool(64 * NST) > 16 ? GramRows::kBranch : GramRows::kDiagonal;
+  constexpr bool kOneTile = tail_pool(64 * NST) <= 16;
   __shared__ PoolShared psh;
   __shared__ int32_t ids[kMaxPool];
   __shared__ float part[4][4][256];
@@ -3699,7 +3699,7 @@ __global__ __launch_bounds__(1024) void k_pool_tail(VoteArgs va, GramArgs a, Max
     while (ti < nt && left >= nt - ti) { left -= nt - ti; ++ti; }
     const int tj = ti + left;
     if (ti < nt) {   // the same for a group of waves
-      const f32x4 acc = gram_quarter<NST, kRows>(a, s, ti, tj, pn, ids, w & 3);
+      const f32x4 acc = gram_quarter<NST, kOneTile>(a, s, ti, tj, pn, ids, w & 3);
 #pragma unroll
       for (int j = 0; j < 4; ++j) part[grp][w & 3][(4 * (lane >> 4) + j) * 16 + (lane & 15)] = acc[j];
     }
