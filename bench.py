@@ -354,7 +354,8 @@ def hot_kernel(cfg, score_mode: int, rows) -> str:
         lists, n = len(rows) * cfg.n_layers * cfg.n_q_heads, max(rows)
         short = (cfg.top_k <= 1024 and n <= 32768 and len(rows) * cfg.n_layers <= 128 and lists <= 512
                  and (n <= 8192 or lists * n <= 3_000_000))
-        return f"k_score_all<{cfg.head_dim}>" if short else f"k_stream<{cfg.head_dim}>"
+        own_prep = "true" if cfg.n_q > 768 else "false"     # the query tiles come from a kernel before it
+        return f"k_score_all<{cfg.head_dim}, {own_prep}>" if short else f"k_stream<{cfg.head_dim}>"
     if score_mode == 1:
         return f"k_stream_hp<{cfg.head_dim}, {cfg.n_kv_heads}>"
     return f"k_stream_hm<{cfg.head_dim}>"
