@@ -2934,8 +2934,9 @@ __device__ void select_list(const ListArgs& a, int list, SelectShared& sh, uint3
 // longer lists are (or, where too many tie for that, all rows by radix).
 // Nothing can be missed, so there is no fallback, and a call for the candidates'
 // statistics takes the streaming pass instead.
-// Measured at 19,200 rows: 9.5 us (loads 2.7, bound and compaction 2.9, selection
-// 2.4), against about 17 us with radix rounds over all 32 slots a thread.
+// Measured at 19,200 rows: 9.5 us by clock stamps (loads 2.7, bound and compaction
+// 2.9, selection 2.4; 11.7 us in the kernel trace), against about 17 us with radix
+// rounds over all 32 slots a thread.
 constexpr int kAllKeep = 4096;   // rows kept by the bound (they take the place of the frame sums)
 constexpr int kAllCloserK = 640; // k from which on a closer bound may be needed
 template <int N, bool CLOSER>
