@@ -1298,6 +1298,10 @@ __global__ __launch_bounds__(8 * D) void k_score_all(PrepArgs pa, ScoreArgs a, A
     bl[i] = bsh[(KS + i) * kWave + lane];
   }
   const bool colv = col < a.G;
+  // A NaN score is at or above no cut-off, so the streaming pass of a sampled list
+  // leaves it out: here it becomes the lowest score.  (Where the sample is the
+  // whole list a NaN ranks by its bits on either route.)
+  const float low = a.samp_step[s] > ((int64_t)1 << 32) ? -INFINITY : __uint_as_float(0x7FC00000u);
   float* out = a.samp + (size_t)(s * a.NL + l * a.Hq + g * a.G + (colv ? col : 0)) * a.samp_stride + 4 * kg;
   for (int t = t0 + wave; t < t1; t += NW * PF) {
 #pragma unroll
@@ -1321,7 +1325,7 @@ __global__ __launch_bounds__(8 * D) void k_score_all(PrepArgs pa, ScoreArgs a, A
       // whole tiles fit the stride (a multiple of 16); rows past n are not read
       if (colv && tt < t1)
         *reinterpret_cast<float4*>(out + (size_t)tt * kTile) =
-            float4{acc[0] + 0.0f, acc[1] + 0.0f, acc[2] + 0.0f, acc[3] + 0.0f};
+            float4{fmaxf(acc[0] + 0.0f, low), fmaxf(acc[1] + 0.0f, low), fmaxf(acc[2] + 0.0f, low), fmaxf(acc[3] + 0.0f, low)};
     }
   }
 }

@@ -131,6 +131,30 @@ def test_stats_are_the_streaming_pass(score_mode, S):
         staged_check(o, q, out, s, k, 4, score_mode=score_mode)
 
 
+@pytest.mark.parametrize("bad", [0x7FC0, 0xFFC0, 0x7F80, 0xFF80])
+@pytest.mark.parametrize("n", [3000, 9000, 20000, 32768])
+def test_non_finite_keys(n, bad):
+    """Three rows with a NaN or an infinity among lists that the other route takes
+    whole (3,000 rows) or samples: the same lists and votes on both, and no NaN
+    row in the sampled ones."""
+    import paper_2609_02780_amd as P
+    T, k = 8, 64
+    rng = np.random.default_rng(n)
+    bits = W.bf16_bits(rng.standard_normal((2, n, 64)).astype(np.float32))
+    rows = [7, n // 2, n - 1]
+    bits[1, rows, [3, 40, 63]] = bad
+    g = P.ShallowIndex(1, 4, 2, 64, n // T, n)
+    g.append([dev_bf16(bits)], n // T, T)
+    q = [dev_bf16(W.bf16_bits(rng.standard_normal((4, 2, 64)).astype(np.float32)))]
+    r = P.Retriever([g], k, 4)
+    a, b = r.debug([q], stats=False), r.debug([q])
+    np.testing.assert_array_equal(a["topk_pos"], b["topk_pos"])
+    np.testing.assert_array_equal(a["vote_hist"], b["vote_hist"])
+    assert (P.sample_plan(n, k)[0] < n) == (n > 4096)
+    if n > 4096 and (bad & 0x7FFF) > 0x7F80:
+        assert not np.isin(a["topk_pos"], rows).any()
+
+
 @pytest.mark.parametrize("T,dup", [(16, 1), (16, 40), (16, 100000)])
 def test_routes_agree(T, dup):
     """The same call on its own route, with a workspace that has no room for every
